@@ -10,7 +10,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libsim_hip.so")
 
-SOURCES = ["sim_kernels.hip", "wsn_kernels.hip", "render_kernels.hip", "sim_api.cpp", "model_pack.cpp"]
+# (source, extra flags): the per-env kernels are compiled once per team width,
+# all at once
+SOURCES = [("team_kernels.hip", [f"-DSIM_TEAM={t}"]) for t in (64, 32, 16, 8, 4, 2, 1)] + [
+    (s, []) for s in ("sim_kernels.hip", "wsn_kernels.hip", "render_kernels.hip", "sim_api.cpp", "model_pack.cpp")]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -25,9 +28,9 @@ def build(verbose: bool = False) -> str:
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
     cmds, objs = [], []
-    for src in SOURCES:
-        obj = os.path.join(bdir, src + ".o")
-        cmds.append([hipcc] + HIPCC_FLAGS + ["-x", "hip", "-I", os.path.join(ROOT, "include"), "-c",
+    for src, extra in SOURCES:
+        obj = os.path.join(bdir, src + "".join(extra) + ".o")
+        cmds.append([hipcc] + HIPCC_FLAGS + extra + ["-x", "hip", "-I", os.path.join(ROOT, "include"), "-c",
                                              os.path.join(CSRC, src), "-o", obj])
         objs.append(obj)
     # the translation units are independent: compile them at once

@@ -25,6 +25,22 @@ struct WgradTile {
 // LDS floats after the env tiles for the controller's per-team offsets
 constexpr int CTRL_SHARED = 128;
 
+// The kernels of one team width, compiled on their own (team_kernels.hip).
+template <int TEAM>
+struct TeamLaunch {
+  static hipError_t rollout(const DevModel& M, const TileSet& ts, int grid, size_t lds, const RolloutArgs& a,
+                            hipStream_t st);
+  static hipError_t rollout_keep(const DevModel& M, const TileSet& ts, int grid, size_t lds, const RolloutArgs& a,
+                                 hipStream_t st);
+  static hipError_t step(const DevModel& M, const TileSet& ts, int grid, size_t lds, const StepArgs& a,
+                         hipStream_t st);
+  static hipError_t grad(const DevModel& M, const TileSet& ts, int grid, size_t lds, const GradArgs& a,
+                         hipStream_t st);
+  static hipError_t recompute(const DevModel& M, const TileSet& ts, int grid, size_t lds, const GradArgs& a,
+                              hipStream_t st);
+  static hipError_t allow_lds(int bytes);   // dynamic LDS limit of this width's kernels
+};
+
 hipError_t launch_zero(int* p, int n, hipStream_t st);
 hipError_t launch_ctrl_transpose(const float* W, float* Wt, int in, int n1, int n2, int no, hipStream_t st);
 hipError_t launch_wgrad(const float* tape, int stride, int n_rows, int chunk, const WgradTile* tiles, int n_tiles,

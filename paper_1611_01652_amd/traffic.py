@@ -37,7 +37,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-KERNEL_SOURCES = ["csrc/sim_kernels.hip", "csrc/step_core.h", "csrc/drivers.h"]
+KERNEL_SOURCES = ["csrc/team_kernels.hip", "csrc/sim_kernels.hip", "csrc/step_core.h", "csrc/drivers.h"]
 # the sources of a workload's kernels where they are not the step's
 WORKLOAD_SOURCES = {"camera": ["csrc/render_kernels.hip"]}
 COPY_MIB = 1024
