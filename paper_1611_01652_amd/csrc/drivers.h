@@ -174,12 +174,9 @@ SHD void loss_adj(const DevModel& M, const Env& E, int t1, const float* p, const
 // they stand after the sweeps (before integration and the impulse store).
 template <class Team>
 SHD void save_step(const Team& tm, const DevModel& M, const Env& E, float* dst) {
+  // (the sweeps wrote the history to dst themselves)
   const int nf = E.lay.total_fwd, nh = align4(M.n_iters * E.nslot);
   for (int i = tm.tl; i < nf / 4; i += tm.ts) st4(dst + 4 * i, ld4(E.L + 4 * i));
-  // (with a history ring the sweeps wrote the history to dst themselves)
-  const float* hs = E.L + E.lay.hist;
-  const int nh4 = E.lay.hring ? 0 : nh / 4;
-  for (int i = tm.tl; i < nh4; i += tm.ts) st4(dst + nf + 4 * i, ld4(hs + 4 * i));
   for (int b = tm.tl; b < E.nb; b += tm.ts)
     for (int k = 0; k < 3; ++k) dst[nf + nh + 3 * b + k] = E.bodyA(b)[AW0 + k];
 }
@@ -214,8 +211,7 @@ SHD void load_step(const Team& tm, const DevModel& M, const Env& E, const float*
   if (b0)
     for (int k = 0; k < 3; ++k) w[k] = src[nf + nh + 3 * tm.tl + k];
   copy_to_lds(tm, E.L, src, nf / 4, E.lay.misc / 4, (E.lay.misc + MISC_N) / 4);
-  // (a history ring is filled sweep by sweep by the sweeps' reverse)
-  if (!E.lay.hring) copy_to_lds(tm, E.L + E.lay.hist, src + nf, nh / 4);
+  // (the sweeps' reverse reads the history from src itself)
   if (b0)
     for (int k = 0; k < 3; ++k) E.bodyA(tm.tl)[AW0 + k] = w[k];
   for (int b = tm.tl + tm.ts; b < E.nb; b += tm.ts) {
@@ -374,11 +370,9 @@ SHD_FLAT void env_rollout_grad(const Team& tm, const DevModel& M, const Env& E, 
     for (int t = t0; !traj && tm.any(t < t1); ++t) {
       const bool act = t < t1;
       if (SAVED) {
-        // (with a history ring the sweeps write the history to the step's
-        // saved working set directly)
+        // (the sweeps write their history to the step's saved working set)
         float* dst = act ? seg + (size_t)(t - t0) * sstride : nullptr;
-        replay_to_sweeps(tm, M, E, a.u, act, t, E.lay.hring ? (dst ? dst + E.lay.total_fwd : nullptr) : E.hist(0),
-                         true);
+        replay_to_sweeps(tm, M, E, a.u, act, t, dst ? dst + E.lay.total_fwd : nullptr, true);
         if (act) save_step(tm, M, E, dst);
         tm.sync();   // the copy reads bodies and rows that integration rewrites
         f_integrate(tm, M, E, act);
@@ -430,7 +424,7 @@ SHD_FLAT void env_rollout_grad(const Team& tm, const DevModel& M, const Env& E, 
       tm.sync();
       a_store(tm, E, act);
       a_integrate(tm, M, E, act);
-      a_pgs(tm, M, E, act,
+      a_pgs<SAVED>(tm, M, E, act,
             (SAVED && act) ? seg + (size_t)(traj ? t : t - t0) * sstride + E.lay.total_fwd : nullptr);
       a_warm(tm, M, E, act);
       a_rows(tm, M, E, act);

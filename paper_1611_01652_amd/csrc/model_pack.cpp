@@ -112,12 +112,10 @@ sim_status build_env(const sim_model_desc& d, int e, bool keep_v, HostEnv& H) {
   H.P = (int)pcode.size();
   // colour-major candidate list
   std::vector<int> colstart, cand;
-  int max_col = 1;
   for (int c = 0; c < njc; ++c) {
     colstart.push_back((int)cand.size());
     for (int j = 0; j < H.nj; ++j)
       if (jcol[j] == c) cand.push_back((K_JOINT << 24) | j);
-    max_col = std::max(max_col, (int)cand.size() - colstart.back());
   }
   for (int k = 0; k < nsub; ++k) {
     colstart.push_back((int)cand.size());
@@ -195,8 +193,9 @@ sim_status build_env(const sim_model_desc& d, int e, bool keep_v, HostEnv& H) {
   }
   H.cst[8 * H.nb + JS * H.nj + 4 * H.G] = d.mu[e];
   H.cst[8 * H.nb + JS * H.nj + 4 * H.G + 1] = d.restitution ? d.restitution[e] : 0.f;
-  // team size: enough lanes for the widest joint colour and half the bodies
-  H.team = std::min(64, next_pow2(std::max({1, max_col, (H.nb + 1) / 2})));
+  // team size: a pair of lanes for every joint (up to the wave), enough lanes
+  // for half the bodies
+  H.team = std::min(64, next_pow2(std::max({1, 2 * H.nj, (H.nb + 1) / 2})));
   int mf = 0, ma = 0;
   if (d.ctrl_kind == 1) {
     const int rec = d.mlp_rec;
@@ -288,6 +287,8 @@ sim_status pack_model(const sim_model_desc* d, PackedModel& P, std::string& err)
   const std::vector<long long>& sz = P.dump == DUMP_TRAJECTORY ? sz_traj
                                      : P.dump == DUMP_SEGMENT  ? sz_segment
                                                                : sz_replay;
+  // the reverse of saved working sets reads the impulse history from them
+  if (P.dump != DUMP_REPLAY) P.adj_of = P.adj_ring_of;
   long long off = 0;
   for (int e = 0; e < E; ++e) {
     if (off / SEG_UNIT > 0x7fffffffLL) { g_msg = nullptr; err = "reverse sweep buffer exceeds 2^31 x 64 floats"; return SIM_E_UNSUPPORTED; }

@@ -404,11 +404,10 @@ sim_status sim_init(const sim_model_desc* d, sim_handle* out) {
     f = (f + 3) & ~3;
     return (f / 4) % 2 == 0 ? f + 4 : f;
   };
-  std::vector<int> fwd_of(E), adj_of(E), adj_ring_of(E);
+  std::vector<int> fwd_of(E), adj_of(E);
   for (int e = 0; e < E; ++e) {
     fwd_of[e] = lds_stride(P.fwd_of[e]);
     adj_of[e] = lds_stride(P.adj_of[e]);
-    adj_ring_of[e] = lds_stride(P.adj_ring_of[e]);
   }
   const long long seg_total = P.seg_total;
   int max_lds = 0;
@@ -420,31 +419,23 @@ sim_status sim_init(const sim_model_desc* d, sim_handle* out) {
     // reverse kernel's registers allow no more).  More envs per CU pay only
     // while the model's envs do not all fit on the device at once: the
     // choice minimises the rounds ceil(E / (CUs x envs per CU)), then takes
-    // no ring over a ring and the narrowest width (the ring costs a read per
-    // sweep and a wider team longer steps).
-    // The reverse of saved working sets may keep only a ring of the impulse
-    // history in LDS (the rest is read from the working set sweep by sweep).
+    // the narrowest width when there is one round (a wider team has longer
+    // steps) and the widest when there are several.
     const int team0 = std::min(64, std::max(team_of[e], d->min_team));
-    int team = -1, ring = 0;
+    int team = -1;
     long long best = 0;
-    for (int r = 0; r < (P.dump != DUMP_REPLAY ? 2 : 1); ++r) {
-      const int fa = r ? adj_ring_of[e] : adj_of[e];
-      for (int t = team0; t <= 64; t *= 2) {
-        if (std::max(adj_bytes(M, t, fa), fwd_bytes(M, t, fwd_of[e], P.ccap_of[e])) > h->max_lds) continue;
-        const long long waves =
-            std::min<long long>(kSimdsPerCu, kLdsPerCu / std::max<long long>(1, adj_bytes(M, t, fa)));
-        const long long envs_cu = (64 / t) * std::max<long long>(1, waves);
-        const long long rounds = ((long long)E + (long long)h->n_cu * envs_cu - 1) / ((long long)h->n_cu * envs_cu);
-        // (equal rounds, more than one: the smaller tile, which packs among
-        // the other buckets' workgroups)
-        if (team < 0 || rounds < best || (rounds == best && rounds > 1 && r == ring && t > team)) {
-          best = rounds; team = t; ring = r;
-        }
+    for (int t = team0; t <= 64; t *= 2) {
+      if (std::max(adj_bytes(M, t, adj_of[e]), fwd_bytes(M, t, fwd_of[e], P.ccap_of[e])) > h->max_lds) continue;
+      const long long waves =
+          std::min<long long>(kSimdsPerCu, kLdsPerCu / std::max<long long>(1, adj_bytes(M, t, adj_of[e])));
+      const long long envs_cu = (64 / t) * std::max<long long>(1, waves);
+      const long long rounds = ((long long)E + (long long)h->n_cu * envs_cu - 1) / ((long long)h->n_cu * envs_cu);
+      // (equal rounds, more than one: the smaller tile, which packs among
+      // the other buckets' workgroups)
+      if (team < 0 || rounds < best || (rounds == best && rounds > 1)) {
+        best = rounds;
+        team = t;
       }
-    }
-    if (ring) {
-      adj_of[e] = adj_ring_of[e];
-      P.hdr[(size_t)e * H_COUNT + H_RING] = 1;
     }
     if (team < 0) {
       release(h);

@@ -181,12 +181,8 @@ struct alignas(16) i4 { int x, y, z, w; };
 struct Lay {
   int body, jc, gs, topo, ws, rows, act_cnt, act_slot, act_code, live, plan, vis, misc, grp, mlp, vsave;  // forward
   int bodyA, rowsA, hist, wsA, jA, mlpA;                                     // adjoint
-  int hring;   // 0: the sweep history of the step in LDS; HRING: a ring of sweeps (the rest in global memory)
   int total_fwd, total;
 };
-// Sweeps of the impulse history held in LDS when the reverse reads the saved
-// working sets: the current sweep's, the previous one's and the one loaded next.
-constexpr int HRING = 3;
 enum { MISC_LOSS = 0, MISC_FLAGS = 1, MISC_NCON = 2, MISC_MU = 3, MISC_GMU = 4, MISC_GMUC = 5, MISC_ITERS = 6,
        MISC_FB = 7, MISC_REST = 8, MISC_N = 12 };
 
@@ -199,13 +195,12 @@ SHD int align4(int x) { return (x + 3) & ~3; }
 enum { JA_DAMP = 0, JA_DAMPC = 1, JA_ANCP = 2, JA_ANCC = 5, JA_ANC_COMP = 6, JA_FLOATS = 14 };
 // mlp_f / mlp_a: controller floats per env (s, h1, h2 / du, d2, d1, sbar), 0 without one
 // vs_f: floats of saved predicted velocities (learned warm start, restitution), 0 without
-// ring: the adjoint layout holds HRING sweeps of the impulse history instead
-// of all of them and the start impulses
+// ghist: the reverse reads the sweeps' impulse history from the saved working
+// sets in global memory; otherwise (replays) the adjoint layout holds it
 SHD Lay make_lay(int nb, int nj, int G, int P, int ncol, int ncand, int nvis, int nslot, int lam, int n_iters,
                  bool adj,
-                 int mlp_f = 0, int mlp_a = 0, int vs_f = 0, bool ring = false) {
+                 int mlp_f = 0, int mlp_a = 0, int vs_f = 0, bool ghist = false) {
   Lay L;
-  L.hring = adj && ring ? HRING : 0;
   int o = 0;
   L.body = o; o += align4((nb + 1) * BS);   // bodies and the world slot (index nb)
   L.jc = o; o += align4(nj * JS);
@@ -227,12 +222,7 @@ SHD Lay make_lay(int nb, int nj, int G, int P, int ncol, int ncand, int nvis, in
   if (adj) {
     L.bodyA = o; o += align4((nb + 1) * BSA);
     L.rowsA = o; o += align4(nslot * RSA);
-    if (L.hring) {
-      L.hist = o; o += align4(HRING * nslot);
-    } else {
-      o += align4(nslot);   // hist(-1): the sweeps' start impulses (reverse only)
-      L.hist = o; o += align4(n_iters * nslot);
-    }
+    L.hist = o; o += ghist ? 0 : align4(n_iters * nslot);
     L.wsA = o; o += align4(lam);
     L.jA = o; o += align4(JA_FLOATS * nj);   // per-joint parameter adjoint totals and compensations
     L.mlpA = o; o += align4(mlp_a);
@@ -268,16 +258,8 @@ struct Env {
   SHD float* wsA() const { return L + lay.wsA; }
   SHD float* row(int s) const { return L + lay.rows + mul24(s, RS); }
   SHD float* rowA(int s) const { return L + lay.rowsA + mul24(s, RSA); }
-  // (it >= -1: the row before the first sweep's holds the start impulses; in
-  // a ring, sweep it sits in slot it mod HRING)
-  SHD float* hist(int it) const {
-    if (lay.hring) {
-      int k = it % HRING;
-      if (k < 0) k += HRING;
-      return L + lay.hist + k * nslot;
-    }
-    return L + lay.hist + it * nslot;
-  }
+  // sweep it's records of the impulse history held in LDS (replays)
+  SHD float* hist(int it) const { return L + lay.hist + it * nslot; }
   SHD int* act_cnt() const { return (int*)(L + lay.act_cnt); }
   SHD int* act_slot() const { return (int*)(L + lay.act_slot); }
   SHD int* act_code() const { return (int*)(L + lay.act_code); }
@@ -345,12 +327,10 @@ SHD Env make_env(const DevModel& M, int ie, float* lds, int n_iters, bool adj) {
   E.gtopo = M.topo + h[H_TOPO];
   E.gcst = M.cst + h[H_CST];
   E.L = lds;
-  // (the reverse of saved working sets may keep a ring of the impulse
-  // history: an env flagged for it in its header)
   E.lay = make_lay(E.nb, E.nj, E.G, E.P, E.ncol, E.ncand, E.nj + E.ccap, E.nslot, E.lam_size, n_iters, adj,
                    mlp_floats_fwd(M),
                    mlp_floats_adj(M), vsave_floats(M.ws_kind || M.has_rest, E.nb),
-                   M.dump != DUMP_REPLAY && h[H_RING] != 0);
+                   M.dump != DUMP_REPLAY);
   return E;
 }
 
@@ -359,6 +339,13 @@ SHD Env make_env(const DevModel& M, int ie, float* lds, int n_iters, bool adj) {
 // the number of (empty) colour passes.
 SHD int n_live(const Env& E, bool act) { return act ? E.live()[0] : 0; }
 SHD int n_plan(const Env& E, bool act) { return act ? E.live()[2 + E.ncol] : 0; }
+// Contacts placed this step: the visit list holds every joint, then them.
+SHD int placed_of_plan(const Env& E) {
+  const int n = E.live()[2 + E.ncol];
+  if (n == 0) return 0;
+  const i4 p = E.plan()[n - 1];
+  return p.x + p.y - E.nj;
+}
 SHD int live_col(const Env& E, int i) { return E.live()[2 + i]; }
 SHD int n_joint_cols(const Env& E, bool act) { return act ? E.live()[1] : 0; }
 
@@ -517,9 +504,18 @@ SHD RowB cand_bodies(const Env& E, int code) {
   return r;
 }
 
+// |(a, b)| with one rounding order wherever it is formed: the reverse sweep
+// recomputes the forward's friction projections and must take its branches.
+SHD float norm2(float a, float b) {
+#if defined(__HIPCC__)
+  return sqrtf(__builtin_fmaf(a, a, b * b));
+#else
+  return sqrtf(a * a + b * b);
+#endif
+}
 // disk projection of the tangent impulse: inside iff |l| <= rho
 SHD void disk(float l1, float l2, float rho, float& o1, float& o2) {
-  const float n = sqrtf(l1 * l1 + l2 * l2);
+  const float n = norm2(l1, l2);
   if (n <= rho) { o1 = l1; o2 = l2; }
   else { const float s = rho / n; o1 = s * l1; o2 = s * l2; }
 }
@@ -1271,52 +1267,152 @@ SHD void f_warm(const Team& tm, const Env& E, bool act) {
   }
 }
 
+// A contact's three rows in registers (ground: body a is the world slot).
+struct ContactRows { RR r[3]; float mt, ima, imb; int s, a, b; };
+template <bool HA>
+SHD void contact_load(ContactRows& c, const Env& E, int s, int a, int b) {
+  c.s = s; c.a = a; c.b = b;
+  for (int q = 0; q < 3; ++q) rr_load(c.r[q], E.row(s + q));
+  c.mt = E.row(s + 3)[XMT];
+  c.ima = HA ? E.body(a)[BIM] : 0.f;
+  c.imb = E.body(b)[BIM];
+}
+SHD void contact_store(const ContactRows& c, const Env& E) {
+  for (int q = 0; q < 3; ++q) E.row(c.s + q)[RL] = c.r[q].lam;
+}
 // One visit of a contact: normal row clamped at 0, then the friction disk.
 // HA = false: a ground contact (body a is the world slot), whose body-a terms
-// are zeros and are skipped (the same bits: x - 0 + 0 is x).
+// are zeros and are skipped (the same bits: x - 0 + 0 is x).  H: the sweep's
+// records (or null).
+template <bool HA>
+SHD void contact_visit(ContactRows& c, const DevModel& M, const Env& E, float mu, float* H, float* rmax = nullptr) {
+  constexpr bool ha = HA;
+  VR V;
+  if constexpr (HA) vr_load_ab(V, E, c.a, c.b);
+  else vr_load_b(V, E, c.b);
+  {
+    RR& r = c.r[0];
+    const float sv_ = rr_jv(r, V, ha) + r.bias + M.gamma * r.lam;
+    const float lt = r.lam - r.m * sv_;
+    const float ln = lt <= 0.f ? 0.f : lt;
+    if (H) H[c.s] = lt;
+    if (rmax) *rmax = fmaxf(*rmax, fabsf(ln - r.lam) / r.m);
+    rr_apply(r, V, ha, c.ima, c.imb, ln - r.lam);
+    r.lam = ln;
+  }
+  RR &r1 = c.r[1], &r2 = c.r[2];
+  const float l1 = r1.lam - c.mt * rr_jv(r1, V, ha);
+  const float l2 = r2.lam - c.mt * rr_jv(r2, V, ha);
+  float n1, n2;
+  disk(l1, l2, mu * c.r[0].lam, n1, n2);
+  if (H) { H[c.s + 1] = l1; H[c.s + 2] = l2; }
+  if (rmax) {
+    const float d1 = n1 - r1.lam, d2 = n2 - r2.lam;
+    *rmax = fmaxf(*rmax, sqrtf(d1 * d1 + d2 * d2) / c.mt);
+  }
+  rr_apply(r1, V, ha, c.ima, c.imb, n1 - r1.lam);
+  rr_apply(r2, V, ha, c.ima, c.imb, n2 - r2.lam);
+  r1.lam = n1;
+  r2.lam = n2;
+  if constexpr (HA) vr_store_ab(V, E, c.a, c.b);
+  else vr_store_b(V, E, c.b);
+}
 template <bool HA = true>
 SHD void pgs_contact(const DevModel& M, const Env& E, int s, int a, int b, float mu, float* H,
                      float* rmax = nullptr) {
-  constexpr bool ha = HA;
-  VR V;
-  if constexpr (HA) vr_load_ab(V, E, a, b);
-  else vr_load_b(V, E, b);
-  RR R[3];
-  for (int q = 0; q < 3; ++q) rr_load(R[q], E.row(s + q));
-  const float mt = E.row(s + 3)[XMT];
-  const float ima = HA ? E.body(a)[BIM] : 0.f, imb = E.body(b)[BIM];
-  {
-    const float sv_ = rr_jv(R[0], V, ha) + R[0].bias + M.gamma * R[0].lam;
-    const float lt = R[0].lam - R[0].m * sv_;
-    const float ln = lt <= 0.f ? 0.f : lt;
-    if (H) H[s] = lt;
-    if (rmax) *rmax = fmaxf(*rmax, fabsf(ln - R[0].lam) / R[0].m);
-    rr_apply(R[0], V, ha, ima, imb, ln - R[0].lam);
-    R[0].lam = ln;
-  }
-  const float l1 = R[1].lam - mt * rr_jv(R[1], V, ha);
-  const float l2 = R[2].lam - mt * rr_jv(R[2], V, ha);
-  float n1, n2;
-  disk(l1, l2, mu * R[0].lam, n1, n2);
-  if (H) { H[s + 1] = l1; H[s + 2] = l2; }
-  if (rmax) {
-    const float d1 = n1 - R[1].lam, d2 = n2 - R[2].lam;
-    *rmax = fmaxf(*rmax, sqrtf(d1 * d1 + d2 * d2) / mt);
-  }
-  rr_apply(R[1], V, ha, ima, imb, n1 - R[1].lam);
-  rr_apply(R[2], V, ha, ima, imb, n2 - R[2].lam);
-  E.row(s)[RL] = R[0].lam;
-  E.row(s + 1)[RL] = n1;
-  E.row(s + 2)[RL] = n2;
-  if constexpr (HA) vr_store_ab(V, E, a, b);
-  else vr_store_b(V, E, b);
+  ContactRows c;
+  contact_load<HA>(c, E, s, a, b);
+  contact_visit<HA>(c, M, E, mu, H, rmax);
+  contact_store(c, E);
 }
 
+// ------------------------------------------------------------------ constraints held by lanes
+// In a team with two lanes per joint, each constraint of the step belongs to
+// lanes that hold its rows in registers over all sweeps: lane pair k (lanes
+// 2k, 2k + 1, one body each) the k-th joint of the visit list, lane q the q-th
+// contact.  A visit then reads and writes only its bodies' velocities in LDS;
+// rows, impulses and, in the reverse, the adjoint accumulators stay in
+// registers, and no visit entry is looked up.  (A single wave issues one
+// instruction per ~4 cycles whatever its kind: per hinge visit the loads,
+// addresses, stores and the list walk were two thirds of the instructions.)
+// A wave where some env has more joints or placed contacts than that walks
+// the visit list instead, rows in LDS.
+template <class Team>
+SHD bool lanes_hold_rows(const Team& tm, const Env& E, bool act) {
+  return !tm.any(act && (2 * E.nj > tm.ts || placed_of_plan(E) > tm.ts));
+}
+// Wave-uniform: the most visits of a sweep among the wave's envs.
+template <class Team>
+SHD int wave_max(const Team& tm, int n) {
+  int m = 0;
+  while (tm.any(n > m)) ++m;
+  return m;
+}
+// What this lane holds: the entries and the visits (plan indices) of its
+// joint and of its contact, -1 without one.
+struct Held { int gh, gc, n; i4 vh, vc; };
+template <class Team>
+SHD Held held_of(const Team& tm, const Env& E, bool act) {
+  Held h;
+  h.gh = h.gc = -1;
+  h.n = n_plan(E, act);
+  h.vh = h.vc = i4{0, 0, 0, 0};
+  const int kh = tm.tl >> 1, kc = E.nj + tm.tl;
+  for (int g = 0; g < h.n; ++g) {
+    const i4 p = E.plan()[g];
+    const int e = p.x + p.y;
+    if (p.z != 0) {
+      if (kh >= p.x && kh < e) h.gh = g;
+    } else if (kc >= p.x && kc < e) {
+      h.gc = g;
+    }
+  }
+  if (h.gh >= 0) h.vh = E.vis()[kh];
+  if (h.gc >= 0) h.vc = E.vis()[kc];
+  return h;
+}
+// A hinge's rows (this lane's side) and impulses in registers.
+struct HingeRows { HSides<1> sd; HR r[6]; float lam[6], hi; int s; };
+template <class Team>
+SHD void hinge_load(const Team& tm, HingeRows& h, const Env& E, const i4& v) {
+  h.s = v.x;
+  h.sd.init(tm, E, v.y, v.z);
+  const float* R0 = E.row(v.x);
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    if (q == 5 && E.jr != 6) break;
+    hr_load(h.r[q], R0 + h.sd.so[0] + q * RS);
+    h.lam[q] = R0[q * RS + RL];
+  }
+  h.hi = E.jr == 6 ? R0[5 * RS + RHI] : 0.f;
+}
+SHD void hinge_store(const HingeRows& h, const Env& E) {
+  float* R0 = E.row(h.s);
+#pragma unroll
+  for (int q = 0; q < 6; ++q)
+    if (q < 5 || E.jr == 6) R0[q * RS + RL] = h.lam[q];
+}
+template <class Team>
+SHD void hinge_visit(const Team& tm, HingeRows& h, const DevModel& M, const Env& E, float* H, float* rmax = nullptr) {
+  HS x;
+  float* B = E.body(h.sd.bd[0]) + BV;
+  hs_load(x, B);
+  // (both lanes of a pair hold and record the same impulses)
+  float* Hw = H ? H + h.s : nullptr;
+  h_row_fwd<0, 1>(tm, M, &h.r[0], &x, h.sd, h.r[0].m, h.r[0].bias, h.lam[0], Hw ? Hw : nullptr, rmax);
+  h_row_fwd<1, 1>(tm, M, &h.r[1], &x, h.sd, h.r[1].m, h.r[1].bias, h.lam[1], Hw ? Hw + 1 : nullptr, rmax);
+  h_row_fwd<2, 1>(tm, M, &h.r[2], &x, h.sd, h.r[2].m, h.r[2].bias, h.lam[2], Hw ? Hw + 2 : nullptr, rmax);
+  h_row_fwd<3, 1>(tm, M, &h.r[3], &x, h.sd, h.r[3].m, h.r[3].bias, h.lam[3], Hw ? Hw + 3 : nullptr, rmax);
+  h_row_fwd<3, 1>(tm, M, &h.r[4], &x, h.sd, h.r[4].m, h.r[4].bias, h.lam[4], Hw ? Hw + 4 : nullptr, rmax);
+  if (E.jr == 6)
+    h_row_box<1>(tm, M, &h.r[5], &x, h.sd, h.r[5].m, h.r[5].bias, h.hi, h.lam[5], Hw ? Hw + 5 : nullptr, rmax);
+  hs_store(x, B);
+}
 // F6: projected Gauss-Seidel sweeps.  With hist, the pre-projection impulse of
 // every row update is recorded there, n_iters rows of nslot floats (in LDS or
 // global memory).
 template <class Team>
-SHD void f_pgs(const Team& tm, const DevModel& M, const Env& E, bool act, float* hist) {
+SHD void f_pgs_listed(const Team& tm, const DevModel& M, const Env& E, bool act, float* hist) {
   const float mu = E.misc()[MISC_MU];
   SweepCursor<1> sw;
   sw.start(tm, E, M.n_iters, n_plan(E, act));
@@ -1339,6 +1435,40 @@ SHD void f_pgs(const Team& tm, const DevModel& M, const Env& E, bool act, float*
     tm.sync();
     sw.advance(vn, p2);
   }
+}
+template <class Team>
+SHD void f_pgs(const Team& tm, const DevModel& M, const Env& E, bool act, float* hist) {
+  if (!lanes_hold_rows(tm, E, act)) {
+    f_pgs_listed(tm, M, E, act, hist);
+    return;
+  }
+  const float mu = E.misc()[MISC_MU];
+  const Held h = held_of(tm, E, act);
+  const bool gnd = h.vc.y == E.nb;
+  HingeRows hr;
+  ContactRows cr;
+  if (h.gh >= 0) hinge_load(tm, hr, E, h.vh);
+  if (h.gc >= 0) {
+    if (gnd) contact_load<false>(cr, E, h.vc.x, h.vc.y, h.vc.z);
+    else contact_load<true>(cr, E, h.vc.x, h.vc.y, h.vc.z);
+  }
+  tm.sync();
+  const int nv = wave_max(tm, h.n);
+  float* H = hist;
+  for (int it = 0; it < M.n_iters; ++it) {
+    for (int g = 0; g < nv; ++g) {
+      if (g == h.gh) hinge_visit(tm, hr, M, E, H);
+      if (g == h.gc) {
+        if (gnd) contact_visit<false>(cr, M, E, mu, H);
+        else contact_visit<true>(cr, M, E, mu, H);
+      }
+      tm.sync();
+    }
+    if (H) H += E.nslot;
+  }
+  if (h.gh >= 0) hinge_store(hr, E);
+  if (h.gc >= 0) contact_store(cr, E);
+  tm.sync();
 }
 
 // F7: semi-implicit Euler and renormalisation of R.
@@ -1846,18 +1976,14 @@ SHD void row_unapply(const float* r, Vel& V, bool ha, float ima, float imb, floa
 // Clear the per-step adjoint accumulators (rows, body extras).
 template <class Team>
 SHD void a_clear_step(const Team& tm, const Env& E, bool act) {
-  // row adjoints and the world slot's adjoint with 16-byte stores (both
-  // regions start on a float4 boundary and span whole float4)
+  // the contacts' row adjoints (placed ones) and the world slot's adjoint with
+  // 16-byte stores (both regions start on a float4 boundary and span whole
+  // float4); a hinge's are written whole by the sweeps' reverse
   static_assert(RSA % 4 == 0 && BSA % 4 == 0, "float4 spans");
   const f4 z{0.f, 0.f, 0.f, 0.f};
-  const int ns4 = act ? E.nslot * (RSA / 4) : 0;
-  for (int i = tm.tl; i < ns4; i += tm.ts) st4(E.rowA(0) + 4 * i, z);
-  // hist(-1) = the start impulses, so that in the reversed sweeps a hinge
-  // row's impulse before its update is the previous sweep's record in every
-  // sweep, the first included
-  // (a ring takes them when it is filled)
-  const int nsl = act && !E.lay.hring ? E.nslot : 0;
-  for (int s = tm.tl; s < nsl; s += tm.ts) E.hist(-1)[s] = E.row(s)[RL0];
+  const int r0 = E.jr * E.nj * (RSA / 4);
+  const int ns4 = act ? r0 + 4 * placed_of_plan(E) * (RSA / 4) : 0;
+  for (int i = r0 + tm.tl; i < ns4; i += tm.ts) st4(E.rowA(0) + 4 * i, z);
   // the world slot's adjoint is a sink of the sweeps: cleared every step so
   // that it stays finite (it only ever meets zero inverse masses)
   const int nw4 = act ? BSA / 4 : 0;
@@ -2148,7 +2274,7 @@ SHD void h_row_rev(const Team& tm, const HR* r, HQ* q, HS* x, HS* A, const HSide
   c.ql = -wv + ltb + gamma * sb;
 }
 // Row q of a visit whose first row is at R0 / Q0 (row slots and adjoint
-// slots) and whose records start at H and Hp.
+// slots) and whose records start at H and Hp (null: the row's start impulse).
 template <int NS>
 SHD void h_rev_load(const HSides<NS>& sd, const float* R0, const float* Q0, int q, const float* H, const float* Hp,
                     HR* r, HQ* qa, HRow& c) {
@@ -2164,7 +2290,7 @@ SHD void h_rev_load(const HSides<NS>& sd, const float* R0, const float* Q0, int 
   c.m = r[0].m; c.bias = r[0].bias;
   c.qm = qa[0].m; c.qb = qa[0].b; c.ql = Q[QL];
   c.lt = H[q];
-  c.lp = Hp[q];
+  c.lp = Hp ? Hp[q] : R[RL0];
 }
 
 // Reverse of a servo's motor row update (see h_row_box): c.lp is the impulse
@@ -2200,11 +2326,11 @@ SHD void h_row_rev_box(const Team& tm, const HR* r, HQ* q, HS* x, HS* A, const H
 // accumulators are streamed: row q-1 is loaded while row q is reversed.
 // A servo's motor row (clamped to [-hi, hi]) is reversed first, on its own.
 // a: body index or the world slot (whose adjoint slot is a sink).  H: this
-// sweep's records, Hp: the previous sweep's (the start impulses before the
-// first sweep).
+// sweep's records, Hp: the previous sweep's (null for the first sweep: the
+// start impulses).  The adjoints accumulate in the row adjoint slots.
 template <int NS, class Team>
 SHD void hinge_rev(const Team& tm, const DevModel& M, const Env& E, int s, int a, int b, const float* H,
-                   const float* Hp, bool first) {
+                   const float* Hp) {
   HSides<NS> sd;
   sd.init(tm, E, a, b);
   HS x[NS], A[NS];
@@ -2217,7 +2343,7 @@ SHD void hinge_rev(const Team& tm, const DevModel& M, const Env& E, int s, int a
   const float* R0 = E.row(s);
   float* Q0 = E.rowA(s);
   const float* Hs = H + s;
-  const float* Hps = Hp + s;
+  const float* Hps = Hp ? Hp + s : nullptr;
   if (E.jr == 6) {
     HR r5[NS];
     HQ q5[NS];
@@ -2226,7 +2352,7 @@ SHD void hinge_rev(const Team& tm, const DevModel& M, const Env& E, int s, int a
     const float hi = R0[5 * RS + RHI];
     // the impulse before this sweep's update: the previous sweep's clamped
     // result, or the start impulse
-    if (!first) c5.lp = c5.lp <= -hi ? -hi : (c5.lp >= hi ? hi : c5.lp);
+    if (Hp) c5.lp = c5.lp <= -hi ? -hi : (c5.lp >= hi ? hi : c5.lp);
     h_row_rev_box<NS>(tm, r5, q5, x, A, sd, c5, M.gamma, hi);
     float* Q = Q0 + 5 * RSA;
     for (int i = 0; i < NS; ++i) {
@@ -2269,45 +2395,66 @@ SHD void hinge_rev(const Team& tm, const DevModel& M, const Env& E, int s, int a
   }
 }
 
-// Reverse of one contact visit: friction disk, then the normal row.  HA =
-// false: a ground contact, body a's terms skipped (they go to the world
-// slot's velocity, zero, and its adjoint, a sink, and to the row's body-a
-// Jacobian adjoints, which a ground contact's set-up adjoint does not read).
-template <bool HA = true>
-SHD void rev_contact(const DevModel& M, const Env& E, int s, int a, int b, float mu, const float* H,
-                     const float* Hp, float& gmu) {
+// The impulses a contact's current sweep left: the records before the
+// projection (lt), the projected ones (n) and the norm of the tangent record.
+struct ContactRec { float lt[3], n[3], nrm; };
+// The projection of a sweep's records: normal clamped at 0, friction disk.
+SHD void contact_project(ContactRec& k, float mu) {
+  k.n[0] = fmaxf(k.lt[0], 0.f);
+  const float rho = mu * k.n[0];
+  k.nrm = norm2(k.lt[1], k.lt[2]);
+  if (k.nrm <= rho) {
+    k.n[1] = k.lt[1];
+    k.n[2] = k.lt[2];
+  } else {
+    const float s = rho / k.nrm;
+    k.n[1] = s * k.lt[1];
+    k.n[2] = s * k.lt[2];
+  }
+}
+// A contact's rows and row adjoints (and that of the friction mass) in registers.
+struct ContactRev { ContactRows c; QR q[3]; float xmt; };
+template <bool HA>
+SHD void contact_rev_load(ContactRev& k, const Env& E, int s, int a, int b) {
+  contact_load<HA>(k.c, E, s, a, b);
+  for (int q = 0; q < 3; ++q) qr_load(k.q[q], E.rowA(s + q));
+  k.xmt = E.rowA(s + 3)[XMT];
+}
+SHD void contact_rev_store(const ContactRev& k, const Env& E) {
+  for (int q = 0; q < 3; ++q) qr_store(k.q[q], E.rowA(k.c.s + q));
+  E.rowA(k.c.s + 3)[XMT] = k.xmt;
+}
+// Reverse of one contact visit: friction disk, then the normal row.  lp: the
+// previous sweep's records (first: the start impulses); on return h holds the
+// previous sweep's impulses.  HA = false: a ground contact, body a's terms
+// skipped (they go to the world slot's velocity, zero, and its adjoint, a
+// sink, and to the row's body-a Jacobian adjoints, which a ground contact's
+// set-up adjoint does not read).
+template <bool HA>
+SHD void contact_rev_visit(ContactRev& k, ContactRec& h, const DevModel& M, const Env& E, float mu, const float* lp,
+                           bool first, float& gmu) {
   constexpr bool ha = HA;
+  const ContactRows& c = k.c;
+  const RR &R0 = c.r[0], &R1 = c.r[1], &R2 = c.r[2];
+  QR &Q0 = k.q[0], &Q1 = k.q[1], &Q2 = k.q[2];
   VR V, A;
   if constexpr (HA) {
-    vr_load_ab(V, E, a, b);
-    vra_load_ab(A, E, a, b);
+    vr_load_ab(V, E, c.a, c.b);
+    vra_load_ab(A, E, c.a, c.b);
   } else {
-    vr_load_b(V, E, b);
-    vra_load_b(A, E, b);
+    vr_load_b(V, E, c.b);
+    vra_load_b(A, E, c.b);
   }
-  RR R1, R2;
-  QR Q1, Q2;
-  rr_load(R1, E.row(s + 1));
-  rr_load(R2, E.row(s + 2));
-  qr_load(Q1, E.rowA(s + 1));
-  qr_load(Q2, E.rowA(s + 2));
-  float* xa = E.rowA(s + 3);
-  const float mt = E.row(s + 3)[XMT];
-  const float ima = HA ? E.body(a)[BIM] : 0.f, imb = E.body(b)[BIM];
+  const float ima = c.ima, imb = c.imb, mt = c.mt;
   float imA = 0.f, imB = 0.f;
-  const float ltn = H[s], l1t = H[s + 1], l2t = H[s + 2];
-  const float ln = fmaxf(ltn, 0.f);
+  const float ltn = h.lt[0], l1t = h.lt[1], l2t = h.lt[2];
+  const float ln = h.n[0], n1 = h.n[1], n2 = h.n[2], nrm = h.nrm;
   const float rho = mu * ln;
-  float n1, n2, p1, p2, lpn;
-  disk(l1t, l2t, rho, n1, n2);
-  if (Hp) {
-    lpn = fmaxf(Hp[s], 0.f);
-    disk(Hp[s + 1], Hp[s + 2], mu * lpn, p1, p2);
-  } else {
-    lpn = E.row(s)[RL0];
-    p1 = E.row(s + 1)[RL0];
-    p2 = E.row(s + 2)[RL0];
-  }
+  for (int q = 0; q < 3; ++q) h.lt[q] = lp[q];
+  if (first)
+    for (int q = 0; q < 3; ++q) h.n[q] = lp[q];
+  else contact_project(h, mu);
+  const float lpn = h.n[0], p1 = h.n[1], p2 = h.n[2];
   const float d1 = n1 - p1, d2 = n2 - p2;
   rr_apply(R2, V, ha, ima, imb, -d2);
   rr_apply(R1, V, ha, ima, imb, -d1);
@@ -2316,7 +2463,6 @@ SHD void rev_contact(const DevModel& M, const Env& E, int s, int a, int b, float
   const float wv1 = rr_wv(R1, A, ha, ima, imb);
   const float wv2 = rr_wv(R2, A, ha, ima, imb);
   const float g1 = Q1.l + wv1, g2 = Q2.l + wv2;
-  const float nrm = sqrtf(l1t * l1t + l2t * l2t);
   float tb1 = g1, tb2 = g2, lnb = 0.f;
   if (!(nrm <= rho)) {
     const float u1 = l1t / nrm, u2 = l2t / nrm, sc = rho / nrm;
@@ -2327,57 +2473,143 @@ SHD void rev_contact(const DevModel& M, const Env& E, int s, int a, int b, float
     lnb = ug * mu;   // adjoint of this iteration's normal impulse
   }
   const float jv1 = rr_jv(R1, V, ha), jv2 = rr_jv(R2, V, ha);
-  xa[XMT] += -(tb1 * jv1 + tb2 * jv2);
+  k.xmt += -(tb1 * jv1 + tb2 * jv2);
   rr_jbar(Q1, R1, A, V, ha, -mt * tb1);
   rr_jbar(Q2, R2, A, V, ha, -mt * tb2);
   Q1.l = -wv1 + tb1;
   Q2.l = -wv2 + tb2;
-  qr_store(Q1, E.rowA(s + 1));
-  qr_store(Q2, E.rowA(s + 2));
-  RR R0;
-  QR Q0;
-  rr_load(R0, E.row(s));
-  qr_load(Q0, E.rowA(s));
   Q0.l += lnb;
   rev_scalar(R0, Q0, V, A, ha, ima, imb, ltn, lpn, false, M.gamma, imA, imB);
-  qr_store(Q0, E.rowA(s));
   if constexpr (HA) {
-    vr_store_ab(V, E, a, b);
-    vra_store_ab(A, E, a, b);
-    E.bodyA(a)[AIM] += imA;
+    vr_store_ab(V, E, c.a, c.b);
+    vra_store_ab(A, E, c.a, c.b);
+    E.bodyA(c.a)[AIM] += imA;
   } else {
-    vr_store_b(V, E, b);
-    vra_store_b(A, E, b);
+    vr_store_b(V, E, c.b);
+    vra_store_b(A, E, c.b);
   }
-  E.bodyA(b)[AIM] += imB;
+  E.bodyA(c.b)[AIM] += imB;
+}
+// The first nr of a constraint's records in a sweep, and its start impulses
+// (in its row slots).  Two functions, so that the records' loads stay global
+// ones: a choice between the two sources makes flat loads, for which every
+// later wait for LDS waits too.
+template <int NR>
+SHD void records(float* l, int nr, int s, const float* H) {
+#pragma unroll
+  for (int q = 0; q < NR; ++q)
+    if (q < nr) l[q] = H[s + q];
+}
+template <int NR>
+SHD void start_impulses(float* l, int nr, const Env& E, int s) {
+#pragma unroll
+  for (int q = 0; q < NR; ++q)
+    if (q < nr) l[q] = E.row(s + q)[RL0];
+}
+// a visit with rows and row adjoints in LDS
+template <bool HA>
+SHD void contact_rev_lds(ContactRec& h, const DevModel& M, const Env& E, int s, int a, int b, float mu,
+                         const float* lp, bool first, float& gmu) {
+  ContactRev k;
+  contact_rev_load<HA>(k, E, s, a, b);
+  contact_rev_visit<HA>(k, h, M, E, mu, lp, first, gmu);
+  contact_rev_store(k, E);
+}
+// ... and records read as they are needed
+template <bool HA>
+SHD void rev_contact(const DevModel& M, const Env& E, int s, int a, int b, float mu, const float* H,
+                     const float* Hp, float& gmu) {
+  ContactRec h;
+  records<3>(h.lt, 3, s, H);
+  contact_project(h, mu);
+  float lp[3];
+  if (Hp) records<3>(lp, 3, s, Hp);
+  else start_impulses<3>(lp, 3, E, s);
+  contact_rev_lds<HA>(h, M, E, s, a, b, mu, lp, Hp == nullptr, gmu);
 }
 
-// Sweep it of the impulse history into its ring slot: from the step's
-// history in global memory, or (it = -1) the start impulses.
+// A hinge's five rows and row adjoints (this lane's side) in registers over
+// the reversed sweeps; c: the row-shared values, with the current sweep's
+// records.  (A servo's motor row stays in LDS: most models have none.)
+struct HingeRev { HSides<1> sd; HR r[5]; HQ q[5]; HRow c[5]; int s; };
 template <class Team>
-SHD void hist_fill(const Team& tm, const Env& E, const float* gh, int it) {
-  float* dst = E.hist(it);
-  if (it >= 0) {
-    const float* src = gh + (size_t)it * E.nslot;
-    for (int s = tm.tl; s < E.nslot; s += tm.ts) dst[s] = src[s];
-  } else {
-    for (int s = tm.tl; s < E.nslot; s += tm.ts) dst[s] = E.row(s)[RL0];
+SHD void hinge_rev_start(const Team& tm, HingeRev& h, const Env& E, const i4& v) {
+  h.s = v.x;
+  h.sd.init(tm, E, v.y, v.z);
+  const float* R0 = E.row(v.x);
+#pragma unroll
+  for (int q = 0; q < 5; ++q) {
+    hr_load(h.r[q], R0 + h.sd.so[0] + q * RS);
+    h.q[q] = HQ{{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, 0.f, 0.f};
+    h.c[q].m = h.r[q].m;
+    h.c[q].bias = h.r[q].bias;
+    h.c[q].qm = h.c[q].qb = 0.f;
+    h.c[q].ql = E.rowA(v.x + q)[QL];
   }
+  if (E.jr == 6) {
+    const HQ z{{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, 0.f, 0.f};
+    hq_store(z, E.rowA(v.x + 5) + h.sd.so[0]);
+  }
+}
+SHD void hinge_rev_store(HingeRev& h, const Env& E) {
+#pragma unroll
+  for (int q = 0; q < 5; ++q) {
+    float* Q = E.rowA(h.s + q);
+    h.q[q].m = h.c[q].qm;
+    h.q[q].b = h.c[q].qb;
+    hq_store(h.q[q], Q + h.sd.so[0]);
+    Q[QL] = h.c[q].ql;
+  }
+}
+// Reverse of one visit of a held hinge; c[].lt the sweep's records, lp the
+// previous sweep's (first: the start impulses); lt5, lp5: a servo's.
+template <class Team>
+SHD void hinge_rev_visit(const Team& tm, HingeRev& h, const DevModel& M, const Env& E, bool first, float lt5,
+                         float lp5) {
+  HS x, A;
+  float imx = 0.f;
+  float* B = E.body(h.sd.bd[0]) + BV;
+  float* Ab = E.bodyA(h.sd.bd[0]);
+  hs_load(x, B);
+  hs_load(A, Ab + AV);
+  if (E.jr == 6) {
+    const float* R = E.row(h.s + 5);
+    float* Q = E.rowA(h.s + 5);
+    HR r5;
+    HQ q5;
+    hr_load(r5, R + h.sd.so[0]);
+    hq_load(q5, Q + h.sd.so[0]);
+    const float hi = R[RHI];
+    HRow c5{r5.m, r5.bias, lt5, lp5, q5.m, q5.b, Q[QL]};
+    if (!first) c5.lp = c5.lp <= -hi ? -hi : (c5.lp >= hi ? hi : c5.lp);
+    h_row_rev_box<1>(tm, &r5, &q5, &x, &A, h.sd, c5, M.gamma, hi);
+    q5.m = c5.qm;
+    q5.b = c5.qb;
+    hq_store(q5, Q + h.sd.so[0]);
+    Q[QL] = c5.ql;
+  }
+  h_row_rev<3, 1>(tm, &h.r[4], &h.q[4], &x, &A, h.sd, &imx, h.c[4], M.gamma);
+  h_row_rev<3, 1>(tm, &h.r[3], &h.q[3], &x, &A, h.sd, &imx, h.c[3], M.gamma);
+  h_row_rev<2, 1>(tm, &h.r[2], &h.q[2], &x, &A, h.sd, &imx, h.c[2], M.gamma);
+  h_row_rev<1, 1>(tm, &h.r[1], &h.q[1], &x, &A, h.sd, &imx, h.c[1], M.gamma);
+  h_row_rev<0, 1>(tm, &h.r[0], &h.q[0], &x, &A, h.sd, &imx, h.c[0], M.gamma);
+  hs_store(x, B);
+  hs_store(A, Ab + AV);
+  Ab[AIM] += imx;
 }
 
 // B6: adjoint of the sweeps (iterations, colours and rows exactly reversed).
-// gh: the step's impulse history in global memory, n_iters rows of nslot
-// floats, when the env keeps only a ring of it in LDS: the last two sweeps
-// are loaded first, and at the start of each reversed sweep it the sweep it-2
-// (or the start impulses) takes the slot sweep it+1 no longer needs.
-template <class Team>
-SHD void a_pgs(const Team& tm, const DevModel& M, const Env& E, bool act, const float* gh = nullptr) {
+// GH: the step's impulse history is in global memory at gh (n_iters rows of
+// nslot floats, the saved working set); otherwise in LDS (replays).
+template <bool GH, class Team>
+SHD void a_pgs_listed(const Team& tm, const DevModel& M, const Env& E, bool act, const float* gh, float& gmu) {
   const float mu = E.misc()[MISC_MU];
-  float gmu = 0.f;
-  const bool ring = E.lay.hring != 0 && act && M.n_iters > 0;
-  if (ring) {
-    hist_fill(tm, E, gh, M.n_iters - 1);
-    hist_fill(tm, E, gh, M.n_iters - 2);
+  if (act) {
+    // the hinges' accumulators start at zero (their impulse adjoints are set)
+    for (int s = tm.tl; s < E.jr * E.nj; s += tm.ts) {
+      float* Q = E.rowA(s);
+      for (int k = 0; k < QJL; ++k) Q[k] = 0.f;
+    }
   }
   tm.sync();
   SweepCursor<-1> sw;
@@ -2385,25 +2617,90 @@ SHD void a_pgs(const Team& tm, const DevModel& M, const Env& E, bool act, const 
   while (tm.any(sw.left > 0)) {
     i4 vn, p2;
     sw.prefetch(tm, E, vn, p2);
-    // (the slot is read by no visit of this sweep; the barrier after the
-    // visit orders the writes before the next sweep's reads)
-    if (ring && sw.left > 0 && sw.ci == sw.nl - 1 && sw.it >= 1) hist_fill(tm, E, gh, sw.it - 2);
-    const float* H = E.hist(sw.it);
-    const float* Hp = E.hist(sw.it - 1);
+    const float* H = (GH ? gh : E.hist(0)) + (long)sw.it * E.nslot;
+    const float* Hp = sw.it > 0 ? H - E.nslot : nullptr;
     const int nk = sw.count(tm);
     for (int k = 0; k < nk; ++k) {
       const i4 v = sw.entry(tm, E, k);
       if (v.x < 0) continue;
       if (cand_kind(v.w) != K_JOINT) {
-        if (v.y == E.nb) rev_contact<false>(M, E, v.x, v.y, v.z, mu, H, sw.it > 0 ? Hp : nullptr, gmu);
-        else rev_contact<true>(M, E, v.x, v.y, v.z, mu, H, sw.it > 0 ? Hp : nullptr, gmu);
+        if (v.y == E.nb) rev_contact<false>(M, E, v.x, v.y, v.z, mu, H, Hp, gmu);
+        else rev_contact<true>(M, E, v.x, v.y, v.z, mu, H, Hp, gmu);
       }
-      else if (tm.ts >= 2) hinge_rev<1>(tm, M, E, v.x, v.y, v.z, H, Hp, sw.it == 0);
-      else hinge_rev<2>(tm, M, E, v.x, v.y, v.z, H, Hp, sw.it == 0);
+      else if (tm.ts >= 2) hinge_rev<1>(tm, M, E, v.x, v.y, v.z, H, Hp);
+      else hinge_rev<2>(tm, M, E, v.x, v.y, v.z, H, Hp);
     }
     tm.sync();
     sw.advance(vn, p2);
   }
+}
+template <bool GH, class Team>
+SHD void a_pgs_held(const Team& tm, const DevModel& M, const Env& E, bool act, const float* gh, float& gmu) {
+  const float mu = E.misc()[MISC_MU];
+  const Held h = held_of(tm, E, act);
+  const bool gnd = h.vc.y == E.nb;
+  auto hist = [&](int it) { return (GH ? gh : E.hist(0)) + (long)it * E.nslot; };   // sweep it's records
+  // Each lane reads its own constraints' records: the current sweep's and
+  // the previous one's are at hand at a visit, and the one before those is
+  // loaded a whole sweep before it is used.
+  HingeRev hr;
+  ContactRev cr;         // a ground contact's rows; a pair's stay in LDS
+  ContactRec hc;
+  float hn[6], hnn[6], cn[3], cnn[3];   // the previous sweep's records, and those of the one before it
+  float lt5 = 0.f;
+  const int n = M.n_iters;
+  if (h.gh >= 0) hinge_rev_start(tm, hr, E, h.vh);
+  if (h.gh >= 0 && n > 0) {
+    float l[6];
+    records<6>(l, E.jr, hr.s, hist(n - 1));
+    if (n >= 2) records<6>(hn, E.jr, hr.s, hist(n - 2));
+    if (n >= 3) records<6>(hnn, E.jr, hr.s, hist(n - 3));
+#pragma unroll
+    for (int q = 0; q < 5; ++q) hr.c[q].lt = l[q];
+    if (E.jr == 6) lt5 = l[5];
+  }
+  if (h.gc >= 0 && gnd) contact_rev_load<false>(cr, E, h.vc.x, h.vc.y, h.vc.z);
+  if (h.gc >= 0 && n > 0) {
+    records<3>(hc.lt, 3, h.vc.x, hist(n - 1));
+    if (n >= 2) records<3>(cn, 3, h.vc.x, hist(n - 2));
+    if (n >= 3) records<3>(cnn, 3, h.vc.x, hist(n - 3));
+    contact_project(hc, mu);
+  }
+  tm.sync();
+  const int nv = wave_max(tm, h.n);
+  for (int it = n - 1; it >= 0; --it) {
+    for (int g = nv - 1; g >= 0; --g) {
+      if (g == h.gc) {
+        if (it == 0) start_impulses<3>(cn, 3, E, h.vc.x);
+        if (gnd) contact_rev_visit<false>(cr, hc, M, E, mu, cn, it == 0, gmu);
+        else contact_rev_lds<true>(hc, M, E, h.vc.x, h.vc.y, h.vc.z, mu, cn, it == 0, gmu);
+        for (int q = 0; q < 3; ++q) cn[q] = cnn[q];
+        if (it >= 3) records<3>(cnn, 3, h.vc.x, hist(it - 3));
+      }
+      if (g == h.gh) {
+        if (it == 0) start_impulses<6>(hn, E.jr, E, hr.s);
+#pragma unroll
+        for (int q = 0; q < 5; ++q) hr.c[q].lp = hn[q];
+        hinge_rev_visit(tm, hr, M, E, it == 0, lt5, hn[5]);
+#pragma unroll
+        for (int q = 0; q < 5; ++q) hr.c[q].lt = hn[q];
+        lt5 = hn[5];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) hn[q] = hnn[q];
+        if (it >= 3) records<6>(hnn, E.jr, hr.s, hist(it - 3));
+      }
+      tm.sync();
+    }
+  }
+  if (h.gh >= 0) hinge_rev_store(hr, E);
+  if (h.gc >= 0 && gnd) contact_rev_store(cr, E);
+  tm.sync();
+}
+template <bool GH, class Team>
+SHD void a_pgs(const Team& tm, const DevModel& M, const Env& E, bool act, const float* gh = nullptr) {
+  float gmu = 0.f;
+  if (lanes_hold_rows(tm, E, act)) a_pgs_held<GH>(tm, M, E, act, gh, gmu);
+  else a_pgs_listed<GH>(tm, M, E, act, gh, gmu);
   // friction coefficient adjoint (one lane per team holds it after a reduction)
   float tot = tm.team_sum(gmu);
   if (tm.tl == 0 && act) kahan_add(E.misc() + MISC_GMU, E.misc() + MISC_GMUC, tot);
