@@ -372,7 +372,7 @@ SHD_FLAT void env_rollout_grad(const Team& tm, const DevModel& M, const Env& E, 
       if (SAVED) {
         // (the sweeps write their history to the step's saved working set)
         float* dst = act ? seg + (size_t)(t - t0) * sstride : nullptr;
-        replay_to_sweeps(tm, M, E, a.u, act, t, dst ? dst + E.lay.total_fwd : nullptr, true);
+        replay_to_sweeps(fresh(tm), M, fresh(E), a.u, act, t, dst ? dst + E.lay.total_fwd : nullptr, true);
         if (act) save_step(tm, M, E, dst);
         tm.sync();   // the copy reads bodies and rows that integration rewrites
         f_integrate(tm, M, E, act);
@@ -386,7 +386,7 @@ SHD_FLAT void env_rollout_grad(const Team& tm, const DevModel& M, const Env& E, 
         for (int i = tm.tl; i < E.lam_size; i += tm.ts) dst[18 * E.nb + i] = E.ws()[i];
       }
       tm.sync();
-      env_step(tm, M, E, (a.u && !M.ctrl) ? a.u + (size_t)t * M.J : nullptr, act, t);
+      env_step(fresh(tm), M, fresh(E), (a.u && !M.ctrl) ? a.u + (size_t)t * M.J : nullptr, act, t);
     }
     tm.sync();
     if (sact && sg == nseg - 1 && tm.tl == 0 && M.loss_kind != 1)
@@ -397,7 +397,7 @@ SHD_FLAT void env_rollout_grad(const Team& tm, const DevModel& M, const Env& E, 
       const bool act = sact && t >= t0;
       if (SAVED) {
         // the saved working set of step t replaces its replay
-        if (act) load_step(tm, M, E, seg + (size_t)(traj ? t : t - t0) * sstride);
+        if (act) load_step(fresh(tm), M, fresh(E), seg + (size_t)(traj ? t : t - t0) * sstride);
         tm.sync();
       } else {
         if (act) {
@@ -407,11 +407,11 @@ SHD_FLAT void env_rollout_grad(const Team& tm, const DevModel& M, const Env& E, 
         }
         tm.sync();
         // replay step t with recording (no integration, no store)
-        replay_to_sweeps(tm, M, E, a.u, act, t, E.hist(0), true);
+        replay_to_sweeps(fresh(tm), M, fresh(E), a.u, act, t, E.hist(0), true);
       }
       // gradient decay of the carry from the later steps (none before the last step)
       if (M.decay != 1.f) {
-        a_decay(tm, M, E, act && t < T - 1);
+        a_decay(fresh(tm), M, fresh(E), act && t < T - 1);
         tm.sync();
       }
       // loss on x^{t+1}: p(t+1) = p(t) + dt v'
@@ -420,20 +420,20 @@ SHD_FLAT void env_rollout_grad(const Team& tm, const DevModel& M, const Env& E, 
         const float p1[3] = {B[BP] + M.dt * B[BV], B[BP + 1] + M.dt * B[BV + 1], B[BP + 2] + M.dt * B[BV + 2]};
         loss_adj(M, E, t + 1, p1, tg, dl, E.bodyA(E.lb) + AP);
       }
-      a_clear_step(tm, E, act);
+      a_clear_step(fresh(tm), fresh(E), act);
       tm.sync();
-      a_store(tm, E, act);
-      a_integrate(tm, M, E, act);
-      a_pgs<SAVED>(tm, M, E, act,
+      a_store(fresh(tm), fresh(E), act);
+      a_integrate(fresh(tm), M, fresh(E), act);
+      a_pgs<SAVED>(fresh(tm), M, fresh(E), act,
             (SAVED && act) ? seg + (size_t)(traj ? t : t - t0) * sstride + E.lay.total_fwd : nullptr);
-      a_warm(tm, M, E, act);
-      a_rows(tm, M, E, act);
+      a_warm(fresh(tm), M, fresh(E), act);
+      a_rows(fresh(tm), M, fresh(E), act);
       // an overflow can later be dropped by a clamp's or a contact's select,
       // so it is caught where it leaves the env: in the control adjoints and
       // the controller's deltas, as each lane writes them
-      a_predict_torques(tm, M, E, act, (act && a.g_u && !M.ctrl) ? a.g_u + (size_t)t * M.J : nullptr, nullptr,
+      a_predict_torques(fresh(tm), M, fresh(E), act, (act && a.g_u && !M.ctrl) ? a.g_u + (size_t)t * M.J : nullptr, nullptr,
                         &bad);
-      a_controller(tm, M, E, act, t, &bad);
+      a_controller(fresh(tm), M, fresh(E), act, t, &bad);
     }
     tm.sync();
   }

@@ -153,8 +153,8 @@ enum { BP = 0, BR = 3, BV = 12, BW = 15, BI = 18, BIM = 24, BII = 25, BTQ = 28, 
 enum { AP = 0, AR = 3, AV = 12, AW = 15, AIW = 18, AIM = 27, AII = 28, ATQ = 31, AW0 = 34,
        ATM = 37, ATI = 38, ACM = 41, ACI = 42, BSA = 48 };
 // joint constants: anchors, axes and perpendiculars (parent, child frames),
-// damping, the step's control, and the servo's gain, torque and rate limits
-enum { JAP = 0, JAC = 3, JXP = 6, JXC = 9, JUP = 12, JUC = 15, JD = 18, JU = 19, JG = 20, JT = 21, JV = 22, JS = 24 };
+// damping, and the servo's gain, torque and rate limits
+enum { JAP = 0, JAC = 3, JXP = 6, JXC = 9, JUP = 12, JUC = 15, JD = 18, JG = 20, JT = 21, JV = 22, JS = 24 };
 // row slot; a contact uses 4 slots: normal, tangent 1, tangent 2, extras.
 // Each body's part of the row is two aligned float4: (Ja, m) (Wa, bias) for
 // body a and (Jb, m) (Wb, bias) for body b, so a lane that handles one body
@@ -179,8 +179,8 @@ enum { QJA = 0, QWA = 4, QJB = 8, QM = 11, QWB = 12, QB = 15, QJL = 16, QL = 19,
 struct alignas(16) i4 { int x, y, z, w; };
 
 struct Lay {
-  int body, jc, gs, topo, ws, rows, act_cnt, act_slot, act_code, live, plan, vis, misc, grp, mlp, vsave;  // forward
-  int bodyA, rowsA, hist, wsA, jA, mlpA;                                     // adjoint
+  int body, jc, gs, topo, ctl, ws, rows, live, plan, vis, misc, cen, mlp, vsave;  // forward
+  int bodyA, rowsA, hist, wsA, jA, mlpA;                                          // adjoint
   int total_fwd, total;
 };
 enum { MISC_LOSS = 0, MISC_FLAGS = 1, MISC_NCON = 2, MISC_MU = 3, MISC_GMU = 4, MISC_GMUC = 5, MISC_ITERS = 6,
@@ -202,22 +202,20 @@ SHD Lay make_lay(int nb, int nj, int G, int P, int ncol, int ncand, int nvis, in
                  int mlp_f = 0, int mlp_a = 0, int vs_f = 0, bool ghist = false) {
   Lay L;
   int o = 0;
-  L.body = o; o += align4((nb + 1) * BS);   // bodies and the world slot (index nb)
   L.jc = o; o += align4(nj * JS);
   L.gs = o; o += align4(G * 4);
   L.topo = o; o += align4(2 * nj + G + P + ncol + 1 + ncand);
+  L.misc = o; o += MISC_N;
+  L.cen = o; o += P > 0 ? 4 * nb : 0;
+  L.body = o; o += align4((nb + 1) * BS);   // bodies and the world slot (index nb)
+  L.ctl = o; o += align4(nj);
   L.ws = o; o += align4(lam);
-  L.rows = o; o += align4(nslot * RS);
-  L.act_cnt = o; o += align4(ncol);
-  L.act_slot = o; o += align4(ncand);
-  L.act_code = o; o += align4(ncand);
-  L.live = o; o += align4(ncol + 3);
+  L.live = o; o += 4;
   L.plan = o; o += 4 * ncol;
   L.vis = o; o += 4 * nvis;   // the constraints a step places: every joint and up to ccap contacts
-  L.misc = o; o += MISC_N;
-  L.grp = o; o += align4(nb + 1);
   L.mlp = o; o += align4(mlp_f);
   L.vsave = o; o += align4(vs_f);
+  L.rows = o; o += align4(nslot * RS);
   L.total_fwd = o;
   if (adj) {
     L.bodyA = o; o += align4((nb + 1) * BSA);
@@ -260,21 +258,17 @@ struct Env {
   SHD float* rowA(int s) const { return L + lay.rowsA + mul24(s, RSA); }
   // sweep it's records of the impulse history held in LDS (replays)
   SHD float* hist(int it) const { return L + lay.hist + it * nslot; }
-  SHD int* act_cnt() const { return (int*)(L + lay.act_cnt); }
-  SHD int* act_slot() const { return (int*)(L + lay.act_slot); }
-  SHD int* act_code() const { return (int*)(L + lay.act_code); }
-  // [0] colours with an active constraint this step, [1] joint colours (the
-  // first colours of the canonical order), [2..2+ncol) the active colours in
-  // order, [2+ncol] the entries of the sweep plan
+  // [0] entries of the sweep plan, [1] joint colours (the first colours of the
+  // canonical order), [2] placed contacts, [3] scratch of the plan's making
   SHD int* live() const { return (int*)(L + lay.live); }
-  // sweep plan of the step (built with the live list): plan()[g] = (start in
-  // vis, count, 1 for hinges, -) for its g-th visit; vis() the step's active
-  // constraints, visit by visit
+  // sweep plan of the step: plan()[g] = (start in vis, count, 1 for hinges, -)
+  // for its g-th visit; vis() the step's constraints, visit by visit: every
+  // joint (the same each step), then the placed contacts in canonical order
   SHD i4* plan() const { return (i4*)(L + lay.plan); }
   SHD i4* vis() const { return (i4*)(L + lay.vis); }
-  // (row set-up) the plan entry that last took each body, the world slot's
-  // included
-  SHD int* grp() const { return (int*)(L + lay.grp); }
+  // (row set-up) world centre and radius of each body's sphere-sphere sphere
+  SHD float* cen(int b) const { return L + lay.cen + 4 * b; }
+  SHD float* ctl() const { return L + lay.ctl; }   // the step's control of each joint
   SHD float* misc() const { return L + lay.misc; }
   SHD float* jA() const { return L + lay.jA; }
   SHD float* mlp() const { return L + lay.mlp; }
@@ -315,6 +309,41 @@ SHD int dump_stride_of(int total_fwd, int n_iters, int nslot, int nb) {
   return total_fwd + align4(n_iters * nslot) + align4(3 * nb);
 }
 
+// The env and the team as one phase of the reverse step sees them: on the GPU,
+// values that the compiler cannot see through, so that what a phase derives
+// from them (LDS addresses, row counts) is formed in that phase.  Hoisted out
+// of the step loop, the phases' hundreds of addresses filled all 512 registers
+// and spilled 520-580 bytes per lane to scratch memory, each reload a memory
+// round trip; formed in place they cost a few instructions and nothing spills.
+// (The forward step fits the registers as it is: there this costs 5 %.)
+#if defined(__HIP_DEVICE_COMPILE__)
+SHD int opaque_zero() {
+  int z = 0;
+  asm volatile("" : "+v"(z));
+  return z;
+}
+SHD Env fresh(const Env& E) {
+  Env F = E;
+  F.L = E.L + opaque_zero();
+  for (int* p : {&F.b0, &F.nb, &F.j0, &F.nj, &F.lam_off, &F.lam_size, &F.G, &F.P, &F.ncol, &F.T, &F.lb, &F.ccap,
+                 &F.ncand, &F.e, &F.nslot, &F.seg_off, &F.tape_off, &F.lam_imp, &F.jr, &F.lay.body, &F.lay.jc,
+                 &F.lay.gs, &F.lay.topo, &F.lay.ctl, &F.lay.ws, &F.lay.rows, &F.lay.live, &F.lay.plan, &F.lay.vis,
+                 &F.lay.misc, &F.lay.cen, &F.lay.mlp, &F.lay.vsave, &F.lay.bodyA, &F.lay.rowsA, &F.lay.hist,
+                 &F.lay.wsA, &F.lay.jA, &F.lay.mlpA, &F.lay.total_fwd, &F.lay.total}) asm volatile("" : "+v"(*p));
+  return F;
+}
+template <class Team>
+SHD Team fresh(const Team& tm) {
+  Team t = tm;
+  t.tl = tm.tl + opaque_zero();
+  return t;
+}
+#else
+SHD const Env& fresh(const Env& E) { return E; }
+template <class Team>
+SHD const Team& fresh(const Team& tm) { return tm; }
+#endif
+
 SHD Env make_env(const DevModel& M, int ie, float* lds, int n_iters, bool adj) {
   const int* h = M.hdr + (size_t)ie * H_COUNT;
   Env E;
@@ -334,24 +363,13 @@ SHD Env make_env(const DevModel& M, int ie, float* lds, int n_iters, bool adj) {
   return E;
 }
 
-// Colours with at least one active constraint this step (built by f_rows):
-// the sweeps visit only these, in canonical order, which changes nothing but
-// the number of (empty) colour passes.
-SHD int n_live(const Env& E, bool act) { return act ? E.live()[0] : 0; }
-SHD int n_plan(const Env& E, bool act) { return act ? E.live()[2 + E.ncol] : 0; }
-// Contacts placed this step: the visit list holds every joint, then them.
-SHD int placed_of_plan(const Env& E) {
-  const int n = E.live()[2 + E.ncol];
-  if (n == 0) return 0;
-  const i4 p = E.plan()[n - 1];
-  return p.x + p.y - E.nj;
-}
-SHD int live_col(const Env& E, int i) { return E.live()[2 + i]; }
+SHD int n_plan(const Env& E, bool act) { return act ? E.live()[0] : 0; }
 SHD int n_joint_cols(const Env& E, bool act) { return act ? E.live()[1] : 0; }
+SHD int n_placed(const Env& E, bool act) { return act ? E.live()[2] : 0; }   // contacts with row slots
 
 // per-env constants in global memory:
 //   bodies  invm[nb], invI[3][nb], pair-sphere offset[3][nb], pair-sphere radius[nb]
-//   joints  20 floats each (JAP..JD layout, JU unused)
+//   joints  JS floats each (JAP..JV layout)
 //   ground  offset(3), radius  per ground sphere
 //   env     mu, restitution
 SHD int cst_joint(const Env& E) { return 8 * E.nb; }
@@ -378,14 +396,21 @@ SHD void load_env_static(const Team& tm, const DevModel& M, const Env& E) {
   for (int i = tm.tl; i < BS; i += tm.ts) E.body(E.nb)[i] = 0.f;
   for (int i = tm.tl; i < JS * E.nj; i += tm.ts) E.L[E.lay.jc + i] = E.gcst[cst_joint(E) + i];
   for (int i = tm.tl; i < 4 * E.G; i += tm.ts) E.L[E.lay.gs + i] = E.gcst[cst_ground(E) + i];
+  // the joints' part of the visit list and of the plan, the same every step
+  const int* gcol = E.gtopo + 2 * E.nj + E.G + E.P;
+  const int* gcand = gcol + E.ncol + 1;
+  for (int k = tm.tl; k < E.nj; k += tm.ts) {
+    const int j = cand_idx(gcand[k]), a = E.gtopo[j];
+    E.vis()[k] = i4{E.jr * j, a >= 0 ? a : E.nb, E.gtopo[E.nj + j], gcand[k]};
+  }
+  for (int c = tm.tl; c < E.ncol; c += tm.ts)
+    if (gcol[c] < E.nj) E.plan()[c] = i4{gcol[c], gcol[c + 1] - gcol[c], 1, 0};
   if (tm.tl == 0) {
     int m = 0;
-    while (m < E.ncol && E.gtopo[2 * E.nj + E.G + E.P + m] < E.gtopo[2 * E.nj + E.G + E.P + m + 1] &&
-           cand_kind(E.gtopo[2 * E.nj + E.G + E.P + E.ncol + 1 + E.gtopo[2 * E.nj + E.G + E.P + m]]) == K_JOINT)
-      ++m;
+    while (m < E.ncol && gcol[m] < E.nj) ++m;
     E.live()[0] = 0;
     E.live()[1] = m;
-    E.live()[2 + E.ncol] = 0;
+    E.live()[2] = 0;
     E.misc()[MISC_MU] = E.gcst[cst_env(E)];
     E.misc()[MISC_REST] = E.gcst[cst_env(E) + 1];
     E.misc()[MISC_LOSS] = 0.f;
@@ -573,7 +598,7 @@ SHD void f_torques(const Team& tm, const Env& E, bool act) {
       f3 wrel = ld3(Bb + BW);
       if (a >= 0) wrel = wrel - ld3(E.body(a) + BW);
       // (a servo's control is its target angle, not a torque)
-      const float tau = (E.jr == 6 ? 0.f : C[JU]) - C[JD] * dot(wrel, n);
+      const float tau = (E.jr == 6 ? 0.f : E.ctl()[j]) - C[JD] * dot(wrel, n);
       add3(Bb + BTQ, tau * n);
       if (a >= 0) add3(E.body(a) + BTQ, -(tau * n));
     }
@@ -634,7 +659,7 @@ SHD void build_joint(const DevModel& M, const Env& E, int j, int s) {
       // gain (theta* - theta), clipped to the rate limit
       const f3 ub = mv(Bb + BR, ld3(C + JUC));
       const float th = atan2f(dot(cross(ua, ub), na), dot(ua, ub));
-      float rate = C[JG] * (C[JU] - th);
+      float rate = C[JG] * (E.ctl()[j] - th);
       if (rate > C[JV]) { rate = C[JV]; clip = 1.f; }
       else if (rate < -C[JV]) { rate = -C[JV]; clip = 1.f; }
       jl = mk3(0.f, 0.f, 0.f);
@@ -684,6 +709,15 @@ SHD void build_joint(const DevModel& M, const Env& E, int j, int s) {
   }
 }
 
+// |d| with one rounding order: f_rows tests candidates with it before it forms
+// the active ones' geometry, and both must decide alike.
+SHD float len3(f3 d) {
+#if defined(__HIPCC__)
+  return sqrtf(__builtin_fmaf(d.z, d.z, __builtin_fmaf(d.x, d.x, d.y * d.y)));
+#else
+  return sqrtf(dot(d, d));
+#endif
+}
 // Gap and geometry of a contact candidate; returns the gap.
 struct CGeo {
   f3 n, ra, rb;   // normal, lever arms (contact point minus body centre)
@@ -711,7 +745,7 @@ SHD CGeo contact_geo(const Env& E, int code) {
     g.ca = ld3(Ba + BP) + mv(Ba + BR, ld3(Ba + BPO));
     g.cb = ld3(Bb + BP) + mv(Bb + BR, ld3(Bb + BPO));
     const f3 d = g.cb - g.ca;
-    g.L = sqrtf(dot(d, d));
+    g.L = len3(d);
     g.gap = g.L - Ba[BPR] - Bb[BPR];
     g.n = g.L < 1e-9f ? mk3(0.f, 0.f, 1.f) : (1.f / g.L) * d;
     g.ra = (g.ca + Ba[BPR] * g.n) - ld3(Ba + BP);
@@ -779,120 +813,108 @@ SHD void build_contact(const DevModel& M, const Env& E, int code, int s, const C
   E.row(s + 2)[RBI] = E.row(s + 2)[RBA] = 0.f;
 }
 
-// F4: per colour, test candidates, compact the active ones, build rows.
-// Inactive contact candidates have their stored impulses cleared.  A colour
-// holds only joints or only contacts.
+// F4: test the contact candidates, compact the active ones, build rows.
+// Inactive contact candidates have their stored impulses cleared.
 //
-// The sweep plan lists the step's visits: each joint colour with an active
-// constraint, and runs of consecutive live contact colours merged into one
-// visit where no constraint of a later colour touches a body that an earlier
-// colour of the run touches (the world slot aside).  Such constraints commute
-// with everything before them in the run (each update reads and writes only
-// its own row and its two bodies), so a merged visit gives the same bits as
-// the colours one after another, with fewer visits per sweep: a long chain's
-// pair contacts fall into many colours with one or two active pairs each.
-// vis() holds the placed constraints contiguously, visit by visit: every
-// active joint and the active contacts that found a row slot (a contact
-// beyond the env's capacity is dropped and the env flagged, and gets no
-// entry), so it needs nj + ccap entries; the colour's active lists
-// (act_code, act_slot, act_cnt) keep every active constraint.
+// Candidates are tested in canonical order, a lane each and as many at a time
+// as the team has lanes (whatever their colour: a colour of a long chain holds
+// a dozen pairs, few of them near, and a pass per colour spent most of the
+// row set-up on its latency).  The sphere centres are formed once per body, and
+// a pair whose squared distance is clearly out of reach takes no root.  The
+// k-th active candidate takes the k-th row slot; beyond the env's capacity it
+// is dropped, its stored impulse cleared and the env flagged.  (Chains of 2..32
+// bodies, forward step: 45 of 103 thousand cycles per wave in a pass per
+// colour; the whole forward-and-reverse call 63.0 -> 58.0 ms.)
+//
+// The sweep plan lists the step's visits: each joint colour, then the placed
+// contacts split into the longest runs of the canonical order in which no two
+// touch one body (the world aside).  Such constraints commute (each update
+// reads and writes only its own row and its two bodies), so a run gives the
+// same bits as its constraints one after another.  A contact ends the open run
+// when the last earlier contact with a body of its own is in that run.
 template <class Team>
 SHD void f_rows(const Team& tm, const DevModel& M, const Env& E, bool act) {
   // Joint rows depend only on the step's body state, so all joints are built
-  // at once, lanes over joints; the colour loop below lists them.
+  // at once, lanes over joints.
   const int nj = act ? E.nj : 0;
   for (int j = tm.tl; j < nj; j += tm.ts) build_joint(M, E, j, E.jr * j);
-  for (int b = tm.tl; b <= (act ? E.nb : -1); b += tm.ts) E.grp()[b] = -2;
+  if (E.P > 0)
+    for (int b = tm.tl; b < (act ? E.nb : 0); b += tm.ts) {
+      const float* B = E.body(b);
+      const f3 c = ld3(B + BP) + mv(B + BR, ld3(B + BPO));
+      st4(E.cen(b), f4{c.x, c.y, c.z, B[BPR]});
+    }
   tm.sync();
-  int ncon = 0;                    // active contacts so far, placed while below ccap (team-uniform)
-  int voff = 0;                    // entries of vis() so far
-  int np = 0;                      // plan entries opened so far
-  int gstart = 0, gcnt = 0, gkind = -1;   // the open plan entry
-  for (int c = 0; tm.any(c < E.ncol && act); ++c) {
-    int lo = 0, hi = 0;
-    if (act && c < E.ncol) { lo = E.colstart(c); hi = E.colstart(c + 1); }
-    const bool jcol = hi > lo && cand_kind(E.cand(lo)) == K_JOINT;
-    int cnt = 0;          // active constraints of this colour
-    int vcnt = 0;         // of them placed (vis entries)
-    bool clash = false;   // this lane's constraints touch a body of the open entry
-    for (int base = lo; tm.any(base < hi); base += tm.ts) {
-      const int i = base + tm.tl;
-      const bool live = i < hi;
-      const int code = live ? E.cand(i) : 0;
-      bool on = false;
-      CGeo g;
-      if (live) {
-        if (jcol) on = true;
-        else {
-          g = contact_geo(E, code);
-          on = g.gap < M.spec;
-          if (!on) {
-            float* w = E.ws() + E.store_of(code);
-            w[0] = w[1] = w[2] = w[3] = 0.f;
-          }
-        }
+  int ncon = 0;   // active contacts so far, placed while below ccap (team-uniform)
+  const int ncc = act ? E.ncand - E.nj : 0;
+  for (int base = 0; tm.any(base < ncc); base += tm.ts) {
+    const int i = base + tm.tl;
+    const bool live = i < ncc;
+    bool on = false;
+    int code = 0;
+    RowB rb{-1, 0};
+    if (live) {
+      code = E.cand(E.nj + i);
+      rb = cand_bodies(E, code);
+      if (cand_kind(code) == K_GROUND) {
+        const float* B = E.body(rb.b);
+        const float* S = E.gsph(cand_idx(code));
+        const f3 c = ld3(B + BP) + mv(B + BR, ld3(S));
+        on = c.z - S[3] < M.spec;
+      } else {
+        const f4 ca = ld4(E.cen(rb.a)), cb = ld4(E.cen(rb.b));
+        const f3 d = mk3(cb.x, cb.y, cb.z) - mk3(ca.x, ca.y, ca.z);
+        const float reach = (ca.w + cb.w + M.spec) * 1.0001f;
+        if (!(reach > 1e-3f) || !(dot(d, d) > reach * reach)) on = len3(d) - ca.w - cb.w < M.spec;
       }
+    }
+    int total = 0;
+    const int q = ncon + tm.prefix(on, total);
+    if (on && q < E.ccap) E.vis()[E.nj + q] = i4{E.jr * E.nj + 4 * q, rb.a >= 0 ? rb.a : E.nb, rb.b, code};
+    if (live && !(on && q < E.ccap)) {
+      float* w = E.ws() + E.store_of(code);
+      w[0] = w[1] = w[2] = w[3] = 0.f;
+      if (on) (*reinterpret_cast<int*>(E.misc() + MISC_FLAGS)) |= 2;
+    }
+    ncon += total;
+  }
+  const int nc = ncon < E.ccap ? ncon : E.ccap;
+  tm.sync();
+  for (int q = tm.tl; q < nc; q += tm.ts) {
+    const i4 v = E.vis()[E.nj + q];
+    build_contact(M, E, v.w, v.x, contact_geo(E, v.w));
+  }
+  int np = n_joint_cols(E, act), start = 0;   // plan entries closed, the open run's first contact
+  for (int base = 0; tm.any(base < nc); base += tm.ts) {
+    const int q = base + tm.tl;
+    int last = -1;   // the last earlier contact with a body of this one
+    if (q < nc) {
+      const i4 v = E.vis()[E.nj + q];
+      for (int p = 0; p < q; ++p) {
+        const i4 o = E.vis()[E.nj + p];
+        if (o.z == v.z || o.z == v.y || (o.y < E.nb && (o.y == v.y || o.y == v.z))) last = p;
+      }
+    }
+    for (;;) {
       int total = 0;
-      const int pos = tm.prefix(on, total);
-      // placed: every joint; the contacts while the capacity lasts, i.e. the
-      // first `room` active ones of this pass (team-uniform)
-      const int room = jcol ? total : (E.ccap - ncon <= 0 ? 0 : (E.ccap - ncon < total ? E.ccap - ncon : total));
-      if (on) {
-        const int li = lo + cnt + pos;   // position in the colour's active list
-        E.act_code()[li] = code;
-        int s = -1;
-        if (jcol) {
-          s = E.jr * cand_idx(code);
-        } else if (pos < room) {
-          s = E.jr * E.nj + 4 * (ncon + pos);
-          build_contact(M, E, code, s, g);
-        } else {
-          // beyond the env's contact capacity: dropped, env flagged
-          float* w = E.ws() + E.store_of(code);
-          w[0] = w[1] = w[2] = w[3] = 0.f;
-          (*reinterpret_cast<int*>(E.misc() + MISC_FLAGS)) |= 2;
-        }
-        E.act_slot()[li] = s;
-        if (pos < room) {
-          const RowB rb = cand_bodies(E, code);
-          E.vis()[voff + vcnt + pos] = i4{s, rb.a >= 0 ? rb.a : E.nb, rb.b, code};
-          if (!jcol) clash = clash || (rb.a >= 0 && E.grp()[rb.a] == np - 1) || E.grp()[rb.b] == np - 1;
-        }
-      }
-      cnt += total;
-      vcnt += room;
-      if (!jcol) ncon += total;
-    }
-    if (act && c < E.ncol) E.act_cnt()[c] = cnt;
-    const bool merge = !tm.team_any(clash) && !jcol && gkind == 0;
-    if (vcnt > 0) {
-      if (!merge) {
-        if (gcnt > 0 && tm.tl == 0) E.plan()[np - 1] = i4{gstart, gcnt, gkind, 0};
+      const bool ends = last >= start;
+      const int pos = tm.prefix(ends, total);
+      if (!tm.any(total > 0)) break;
+      if (ends && pos == 0) E.live()[3] = q;
+      tm.sync();
+      if (total > 0) {
+        const int next = E.live()[3];
+        if (tm.tl == 0) E.plan()[np] = i4{E.nj + start, next - start, 0, 0};
         ++np;
-        gstart = voff;
-        gcnt = 0;
-        gkind = jcol ? 1 : 0;
+        start = next;
       }
-      gcnt += vcnt;
-      // the open entry's bodies: this colour's constraints touch distinct
-      // bodies (the world slot aside, which is not marked)
-      if (!jcol)
-        for (int k = tm.tl; k < vcnt; k += tm.ts) {
-          const i4 v = E.vis()[voff + k];
-          E.grp()[v.z] = np - 1;
-          if (v.y < E.nb) E.grp()[v.y] = np - 1;
-        }
-      voff += vcnt;
+      tm.sync();
     }
-    tm.sync();
   }
   if (act && tm.tl == 0) {
-    if (gcnt > 0) E.plan()[np - 1] = i4{gstart, gcnt, gkind, 0};
-    E.live()[2 + E.ncol] = np;
-    int m = 0;
-    for (int c = 0; c < E.ncol; ++c)
-      if (E.act_cnt()[c] > 0) E.live()[2 + m++] = c;
-    E.live()[0] = m;
+    if (nc > 0) E.plan()[np] = i4{E.nj + start, nc - start, 0, 0};
+    E.live()[0] = np + (nc > 0 ? 1 : 0);
+    E.live()[2] = nc;
   }
   tm.sync();
 }
@@ -1136,11 +1158,22 @@ SHD void h_apply(const HR& r, HS& x, float sim, float d) {
   if (S < 3) x.v[S] += sim * d;
   for (int k = 0; k < 3; ++k) x.w[k] += d * r.W[k];
 }
+// The rows' side parts where a residual is wanted (tolerance mode): the sign
+// is a select, not a factor, so that the one product to fuse is j0 w0 in both
+// forms and sweep counts do not depend on the form.
+template <int S>
+SHD float h_jpart_sel(const HR& r, const HS& x, float sg) {
+  float p = S < 3 ? (sg < 0.f ? -x.v[S] : x.v[S]) : 0.f;
+  p += r.j[0] * x.w[0];
+  p += r.j[1] * x.w[1];
+  p += r.j[2] * x.w[2];
+  return p;
+}
 template <int S, int NS, class Team>
 SHD void h_row_fwd(const Team& tm, const DevModel& M, const HR* r, HS* x, const HSides<NS>& sd, float m, float bias,
                    float& lam, float* h, float* rmax) {
   float p[NS];
-  for (int i = 0; i < NS; ++i) p[i] = h_jpart<S>(r[i], x[i], sd.sg[i]);
+  for (int i = 0; i < NS; ++i) p[i] = rmax ? h_jpart_sel<S>(r[i], x[i], sd.sg[i]) : h_jpart<S>(r[i], x[i], sd.sg[i]);
   const float sv_ = h_sum<NS>(tm, p) + bias + M.gamma * lam;
   const float lt = lam - m * sv_;
   if (h) *h = lt;
@@ -1282,10 +1315,10 @@ SHD void contact_store(const ContactRows& c, const Env& E) {
 }
 // One visit of a contact: normal row clamped at 0, then the friction disk.
 // HA = false: a ground contact (body a is the world slot), whose body-a terms
-// are zeros and are skipped (the same bits: x - 0 + 0 is x).  H: the sweep's
-// records (or null).
+// are zeros and are skipped (the same bits: x - 0 + 0 is x).  rec: where the
+// rows' impulses before the projection are recorded (or null).
 template <bool HA>
-SHD void contact_visit(ContactRows& c, const DevModel& M, const Env& E, float mu, float* H, float* rmax = nullptr) {
+SHD void contact_visit(ContactRows& c, const DevModel& M, const Env& E, float mu, float* rec, float* rmax = nullptr) {
   constexpr bool ha = HA;
   VR V;
   if constexpr (HA) vr_load_ab(V, E, c.a, c.b);
@@ -1295,7 +1328,7 @@ SHD void contact_visit(ContactRows& c, const DevModel& M, const Env& E, float mu
     const float sv_ = rr_jv(r, V, ha) + r.bias + M.gamma * r.lam;
     const float lt = r.lam - r.m * sv_;
     const float ln = lt <= 0.f ? 0.f : lt;
-    if (H) H[c.s] = lt;
+    if (rec) rec[0] = lt;
     if (rmax) *rmax = fmaxf(*rmax, fabsf(ln - r.lam) / r.m);
     rr_apply(r, V, ha, c.ima, c.imb, ln - r.lam);
     r.lam = ln;
@@ -1305,7 +1338,7 @@ SHD void contact_visit(ContactRows& c, const DevModel& M, const Env& E, float mu
   const float l2 = r2.lam - c.mt * rr_jv(r2, V, ha);
   float n1, n2;
   disk(l1, l2, mu * c.r[0].lam, n1, n2);
-  if (H) { H[c.s + 1] = l1; H[c.s + 2] = l2; }
+  if (rec) { rec[1] = l1; rec[2] = l2; }
   if (rmax) {
     const float d1 = n1 - r1.lam, d2 = n2 - r2.lam;
     *rmax = fmaxf(*rmax, sqrtf(d1 * d1 + d2 * d2) / c.mt);
@@ -1322,7 +1355,7 @@ SHD void pgs_contact(const DevModel& M, const Env& E, int s, int a, int b, float
                      float* rmax = nullptr) {
   ContactRows c;
   contact_load<HA>(c, E, s, a, b);
-  contact_visit<HA>(c, M, E, mu, H, rmax);
+  contact_visit<HA>(c, M, E, mu, H ? H + s : nullptr, rmax);
   contact_store(c, E);
 }
 
@@ -1339,7 +1372,7 @@ SHD void pgs_contact(const DevModel& M, const Env& E, int s, int a, int b, float
 // the visit list instead, rows in LDS.
 template <class Team>
 SHD bool lanes_hold_rows(const Team& tm, const Env& E, bool act) {
-  return !tm.any(act && (2 * E.nj > tm.ts || placed_of_plan(E) > tm.ts));
+  return !tm.any(act && (2 * E.nj > tm.ts || n_placed(E, act) > tm.ts));
 }
 // Wave-uniform: the most visits of a sweep among the wave's envs.
 template <class Team>
@@ -1393,12 +1426,12 @@ SHD void hinge_store(const HingeRows& h, const Env& E) {
     if (q < 5 || E.jr == 6) R0[q * RS + RL] = h.lam[q];
 }
 template <class Team>
-SHD void hinge_visit(const Team& tm, HingeRows& h, const DevModel& M, const Env& E, float* H, float* rmax = nullptr) {
+SHD void hinge_visit(const Team& tm, HingeRows& h, const DevModel& M, const Env& E, float* rec, float* rmax = nullptr) {
   HS x;
   float* B = E.body(h.sd.bd[0]) + BV;
   hs_load(x, B);
   // (both lanes of a pair hold and record the same impulses)
-  float* Hw = H ? H + h.s : nullptr;
+  float* Hw = rec;
   h_row_fwd<0, 1>(tm, M, &h.r[0], &x, h.sd, h.r[0].m, h.r[0].bias, h.lam[0], Hw ? Hw : nullptr, rmax);
   h_row_fwd<1, 1>(tm, M, &h.r[1], &x, h.sd, h.r[1].m, h.r[1].bias, h.lam[1], Hw ? Hw + 1 : nullptr, rmax);
   h_row_fwd<2, 1>(tm, M, &h.r[2], &x, h.sd, h.r[2].m, h.r[2].bias, h.lam[2], Hw ? Hw + 2 : nullptr, rmax);
@@ -1408,6 +1441,7 @@ SHD void hinge_visit(const Team& tm, HingeRows& h, const DevModel& M, const Env&
     h_row_box<1>(tm, M, &h.r[5], &x, h.sd, h.r[5].m, h.r[5].bias, h.hi, h.lam[5], Hw ? Hw + 5 : nullptr, rmax);
   hs_store(x, B);
 }
+
 // F6: projected Gauss-Seidel sweeps.  With hist, the pre-projection impulse of
 // every row update is recorded there, n_iters rows of nslot floats (in LDS or
 // global memory).
@@ -1454,17 +1488,18 @@ SHD void f_pgs(const Team& tm, const DevModel& M, const Env& E, bool act, float*
   }
   tm.sync();
   const int nv = wave_max(tm, h.n);
-  float* H = hist;
+  float* rh = hist ? hist + h.vh.x : nullptr;
+  float* rc = hist ? hist + h.vc.x : nullptr;
   for (int it = 0; it < M.n_iters; ++it) {
     for (int g = 0; g < nv; ++g) {
-      if (g == h.gh) hinge_visit(tm, hr, M, E, H);
+      if (g == h.gh) hinge_visit(tm, hr, M, E, rh);
       if (g == h.gc) {
-        if (gnd) contact_visit<false>(cr, M, E, mu, H);
-        else contact_visit<true>(cr, M, E, mu, H);
+        if (gnd) contact_visit<false>(cr, M, E, mu, rc);
+        else contact_visit<true>(cr, M, E, mu, rc);
       }
       tm.sync();
     }
-    if (H) H += E.nslot;
+    if (hist) { rh += E.nslot; rc += E.nslot; }
   }
   if (h.gh >= 0) hinge_store(hr, E);
   if (h.gc >= 0) contact_store(cr, E);
@@ -1556,7 +1591,7 @@ template <class Team>
 SHD void f_controls(const Team& tm, const DevModel& M, const Env& E, const float* u_row, bool act, int t = 0) {
   const int nj = act ? E.nj : 0;
   if (!M.ctrl) {
-    for (int j = tm.tl; j < nj; j += tm.ts) E.jc(j)[JU] = u_row ? u_row[E.j0 + j] : 0.f;
+    for (int j = tm.tl; j < nj; j += tm.ts) E.ctl()[j] = u_row ? u_row[E.j0 + j] : 0.f;
     return;
   }
   float* sv_ = E.mlp();
@@ -1579,7 +1614,7 @@ SHD void f_controls(const Team& tm, const DevModel& M, const Env& E, const float
   // ignores)
   tm.ctrl_forward(M, E);
   const float* u = sv_ + mo_u(M);
-  for (int i = tm.tl; i < nj; i += tm.ts) E.jc(i)[JU] = u[i];
+  for (int i = tm.tl; i < nj; i += tm.ts) E.ctl()[i] = u[i];
   // h^{t+1} = tanh(a) replaces h^t in the carried state (nothing later in the
   // step reads h)
   for (int i = tm.tl; i < rec; i += tm.ts) E.ws()[E.lam_imp + i] = tanhf(u[E.nj + i]);
@@ -1639,27 +1674,17 @@ struct RecArgs {
   int every;                     // steps t with t % every == 0
 };
 
-SHD bool is_contact_colour(const Env& E, int c) {
-  const int lo = E.colstart(c), hi = E.colstart(c + 1);
-  return hi > lo && cand_kind(E.cand(lo)) != K_JOINT;
-}
-
 // Warm-start features of every active contact, at the predicted velocities
 // and the plain warm-start impulses, into its extras slot: gap / dt, J v of the
 // normal and both tangent rows, and the three plain impulses over their
 // effective masses.
 template <class Team>
 SHD void f_features(const Team& tm, const DevModel& M, const Env& E, bool act) {
-  const int nl = n_live(E, act);
-  for (int ci = 0; tm.any(ci < nl); ++ci) {
-    const int c = ci < nl ? live_col(E, ci) : 0;
-    const bool cc = ci < nl && is_contact_colour(E, c);
-    const int n = cc ? E.act_cnt()[c] : 0;
-    const int lo = cc ? E.colstart(c) : 0;
-    for (int k = tm.tl; k < n; k += tm.ts) {
-      const int s = E.act_slot()[lo + k];
-      if (s < 0) continue;
-      const RowB rb = cand_bodies(E, E.act_code()[lo + k]);
+  const int nc = n_placed(E, act);
+  for (int q = tm.tl; q < nc; q += tm.ts) {
+      const i4 v = E.vis()[E.nj + q];
+      const int s = v.x;
+      const RowB rb{v.y == E.nb ? -1 : v.y, v.z};
       const bool ha = rb.a >= 0;
       VR V;
       vr_load(V, E, rb.a, rb.b);
@@ -1676,7 +1701,6 @@ SHD void f_features(const Team& tm, const DevModel& M, const Env& E, bool act) {
       x[XF + 4] = E.row(s)[RL0] / R0.m;
       x[XF + 5] = E.row(s + 1)[RL0] / mt;
       x[XF + 6] = E.row(s + 2)[RL0] / mt;
-    }
   }
   tm.sync();
 }
@@ -1695,18 +1719,9 @@ SHD void f_save_vel(const Team& tm, const Env& E, bool act) {
 // impulses (in velocity units: impulse over effective mass), and the result,
 // projected onto lambda_n >= 0, |lambda_t| <= mu lambda_n, replaces the
 // contacts' warm-start impulses.
-// Contacts placed in row slots (team-uniform): the first ccap active contacts
-// in colour-major order; any beyond the capacity were dropped and flagged.
-SHD int placed_contacts(const Env& E, bool act) {
-  int n = 0;
-  for (int c = 0; c < E.ncol && act; ++c)
-    if (is_contact_colour(E, c)) n += E.act_cnt()[c];
-  return n < E.ccap ? n : E.ccap;
-}
-
 template <class Team>
 SHD void f_learned_ws(const Team& tm, const DevModel& M, const Env& E, bool act) {
-  const int n_e = placed_contacts(E, act);
+  const int n_e = n_placed(E, act);
   int* cnt = tm.shared_cnt();
   int* map = tm.shared_map();
   if (tm.tl == 0) cnt[tm.team] = act ? n_e : 0;
@@ -1717,29 +1732,13 @@ SHD void f_learned_ws(const Team& tm, const DevModel& M, const Env& E, bool act)
     if (q < tm.team) base += v;
     total += v;
   }
-  int idx = base;
-  const int nl = n_live(E, act);
-  for (int ci = 0; tm.any(ci < nl); ++ci) {
-    const int c = ci < nl ? live_col(E, ci) : 0;
-    const bool cc = ci < nl && is_contact_colour(E, c);
-    const int n = cc ? E.act_cnt()[c] : 0;
-    const int lo = cc ? E.colstart(c) : 0;
-    for (int k = tm.tl; k < n; k += tm.ts)
-      if (idx + k < base + n_e) map[idx + k] = (int)(E.row(E.act_slot()[lo + k] + 3) - tm.lds0);
-    idx += n;
-  }
+  for (int q = tm.tl; q < n_e; q += tm.ts) map[base + q] = (int)(E.row(E.vis()[E.nj + q].x + 3) - tm.lds0);
   tm.sync();
   tm.wsn_rows(total, map);
   tm.sync();
   const float mu = E.misc()[MISC_MU];
-  for (int ci = 0; tm.any(ci < nl); ++ci) {
-    const int c = ci < nl ? live_col(E, ci) : 0;
-    const bool cc = ci < nl && is_contact_colour(E, c);
-    const int n = cc ? E.act_cnt()[c] : 0;
-    const int lo = cc ? E.colstart(c) : 0;
-    for (int k = tm.tl; k < n; k += tm.ts) {
-      const int s = E.act_slot()[lo + k];
-      if (s < 0) continue;
+  for (int q = tm.tl; q < n_e; q += tm.ts) {
+      const int s = E.vis()[E.nj + q].x;
       // outputs: corrections to the carried impulses over their effective masses
       const float* x = E.row(s + 3);
       const float ln = fmaxf(E.row(s)[RM] * (x[XF + 4] + x[XY]), 0.f);
@@ -1749,7 +1748,6 @@ SHD void f_learned_ws(const Team& tm, const DevModel& M, const Env& E, bool act)
       E.row(s)[RL] = E.row(s)[RL0] = ln;
       E.row(s + 1)[RL] = E.row(s + 1)[RL0] = l1;
       E.row(s + 2)[RL] = E.row(s + 2)[RL0] = l2;
-    }
   }
   tm.sync();
 }
@@ -1761,24 +1759,18 @@ SHD void f_restart(const Team& tm, const DevModel& M, const Env& E, bool act) {
   if (act)
     for (int b = tm.tl; b < E.nb; b += tm.ts)
       for (int k = 0; k < 6; ++k) E.body(b)[BV + k] = E.vsave(b)[k];
-  const int nl = n_live(E, act);
-  for (int ci = 0; tm.any(ci < nl); ++ci) {
-    const int c = ci < nl ? live_col(E, ci) : 0;
-    const int n = ci < nl ? E.act_cnt()[c] : 0;
-    const int lo = ci < nl ? E.colstart(c) : 0;
-    for (int k = tm.tl; k < n; k += tm.ts) {
-      const int s = E.act_slot()[lo + k];
-      if (s < 0) continue;
-      if (cand_kind(E.act_code()[lo + k]) == K_JOINT) {
-        for (int q = 0; q < E.jr; ++q) E.row(s + q)[RL] = E.row(s + q)[RL0];
-      } else {
-        const float* x = E.row(s + 3);
-        const float* w = E.ws() + *reinterpret_cast<const int*>(x + XSTORE);
-        const f3 Lt = mk3(w[1], w[2], w[3]);
-        E.row(s)[RL] = E.row(s)[RL0] = M.warm * w[0];
-        E.row(s + 1)[RL] = E.row(s + 1)[RL0] = M.warm * dot(ld3(x + XT1), Lt);
-        E.row(s + 2)[RL] = E.row(s + 2)[RL0] = M.warm * dot(ld3(x + XT2), Lt);
-      }
+  const int n = act ? E.nj + n_placed(E, act) : 0;
+  for (int k = tm.tl; k < n; k += tm.ts) {
+    const int s = E.vis()[k].x;
+    if (k < E.nj) {
+      for (int q = 0; q < E.jr; ++q) E.row(s + q)[RL] = E.row(s + q)[RL0];
+    } else {
+      const float* x = E.row(s + 3);
+      const float* w = E.ws() + *reinterpret_cast<const int*>(x + XSTORE);
+      const f3 Lt = mk3(w[1], w[2], w[3]);
+      E.row(s)[RL] = E.row(s)[RL0] = M.warm * w[0];
+      E.row(s + 1)[RL] = E.row(s + 1)[RL0] = M.warm * dot(ld3(x + XT1), Lt);
+      E.row(s + 2)[RL] = E.row(s + 2)[RL0] = M.warm * dot(ld3(x + XT2), Lt);
     }
   }
   tm.sync();
@@ -1792,23 +1784,36 @@ template <class Team>
 SHD void f_pgs_tol(const Team& tm, const DevModel& M, const Env& E, bool live, int& it, float& res, int limit,
                    float* res_c = nullptr) {
   const float mu = E.misc()[MISC_MU];
+  const bool held = lanes_hold_rows(tm, E, live);
+  const Held h = held_of(tm, E, live);
+  const bool gnd = h.vc.y == E.nb;
+  HingeRows hr;
+  ContactRows cr;
+  if (held && h.gh >= 0) hinge_load(tm, hr, E, h.vh);
+  if (held && h.gc >= 0) {
+    if (gnd) contact_load<false>(cr, E, h.vc.x, h.vc.y, h.vc.z);
+    else contact_load<true>(cr, E, h.vc.x, h.vc.y, h.vc.z);
+  }
+  tm.sync();
   for (;;) {
     const bool run = live && res > M.tol && it < limit;
     if (!tm.any(run)) break;
     float r = 0.f, rc = 0.f;
-    const int nl = n_live(E, run);
+    const int nl = run ? h.n : 0;
     for (int ci = 0; tm.any(ci < nl); ++ci) {
-      const int c = ci < nl ? live_col(E, ci) : 0;
-      const int n = ci < nl ? E.act_cnt()[c] : 0;
-      const int lo = ci < nl ? E.colstart(c) : 0;
-      for (int k = tm.tl; k < n; k += tm.ts) {
-        const int s = E.act_slot()[lo + k];
-        if (s < 0) continue;
-        const int code = E.act_code()[lo + k];
-        const RowB rb = cand_bodies(E, code);
-        const int a = rb.a >= 0 ? rb.a : E.nb;
-        if (cand_kind(code) == K_JOINT) hinge_fwd<2>(tm, M, E, s, a, rb.b, nullptr, &r);
-        else pgs_contact(M, E, s, a, rb.b, mu, nullptr, &rc);
+      if (held) {
+        if (run && ci == h.gh) hinge_visit(tm, hr, M, E, nullptr, &r);
+        if (run && ci == h.gc) {
+          if (gnd) contact_visit<false>(cr, M, E, mu, nullptr, &rc);
+          else contact_visit<true>(cr, M, E, mu, nullptr, &rc);
+        }
+      } else if (ci < nl) {
+        const i4 p = E.plan()[ci];
+        for (int k = tm.tl; k < p.y; k += tm.ts) {
+          const i4 v = E.vis()[p.x + k];
+          if (p.z != 0) hinge_fwd<2>(tm, M, E, v.x, v.y, v.z, nullptr, &r);
+          else pgs_contact(M, E, v.x, v.y, v.z, mu, nullptr, &rc);
+        }
       }
       tm.sync();
     }
@@ -1818,6 +1823,9 @@ SHD void f_pgs_tol(const Team& tm, const DevModel& M, const Env& E, bool live, i
       ++it;
     }
   }
+  if (held && h.gh >= 0) hinge_store(hr, E);
+  if (held && h.gc >= 0) contact_store(cr, E);
+  tm.sync();
 }
 
 // One record per active contact of a converged step: features, converged
@@ -1825,19 +1833,13 @@ SHD void f_pgs_tol(const Team& tm, const DevModel& M, const Env& E, bool live, i
 // three as int32 bit patterns).
 template <class Team>
 SHD void f_records(const Team& tm, const DevModel& M, const Env& E, bool act, int t, const RecArgs& ra) {
-  const int n_e = placed_contacts(E, act);
+  const int n_e = n_placed(E, act);
   const unsigned long long base = tm.reserve(ra.count, act ? n_e : 0);
-  long long idx = (long long)base;
-  const int nl = n_live(E, act);
-  for (int ci = 0; tm.any(ci < nl); ++ci) {
-    const int c = ci < nl ? live_col(E, ci) : 0;
-    const bool cc = ci < nl && is_contact_colour(E, c);
-    const int n = cc ? E.act_cnt()[c] : 0;
-    const int lo = cc ? E.colstart(c) : 0;
-    for (int k = tm.tl; k < n; k += tm.ts) {
-      const int s = E.act_slot()[lo + k];
-      const long long i = idx + k;
-      if (s < 0 || i >= ra.cap) continue;
+  for (int k = tm.tl; k < n_e; k += tm.ts) {
+      const i4 v = E.vis()[E.nj + k];
+      const int s = v.x;
+      const long long i = (long long)base + k;
+      if (i >= ra.cap) continue;
       const float* x = E.row(s + 3);
       const float mn = E.row(s)[RM], mt = x[XMT];
       float* o = ra.rec + (size_t)i * 16;
@@ -1849,10 +1851,8 @@ SHD void f_records(const Team& tm, const DevModel& M, const Env& E, bool act, in
       o[11] = mt;
       *reinterpret_cast<int*>(o + 12) = E.e;
       *reinterpret_cast<int*>(o + 13) = t;
-      *reinterpret_cast<int*>(o + 14) = E.act_code()[lo + k];
+      *reinterpret_cast<int*>(o + 14) = v.w;
       o[15] = 0.f;
-    }
-    idx += n;
   }
 }
 
@@ -1874,9 +1874,7 @@ SHD void env_step_solve(const Team& tm, const DevModel& M, const Env& E, const f
   if (M.ws_kind || rec) f_features(tm, M, E, act);
   if (M.ws_kind) f_learned_ws(tm, M, E, act);
   f_warm(tm, E, act);
-  int nrows = 0;
-  for (int c = 0; c < E.ncol && act; ++c) nrows += E.act_cnt()[c];
-  const bool live = act && nrows > 0;
+  const bool live = n_plan(E, act) > 0;
   int it = 0, wasted = 0, fb = 0;
   float res = 3.0e38f;
   if (M.ws_kind) {
@@ -1982,7 +1980,7 @@ SHD void a_clear_step(const Team& tm, const Env& E, bool act) {
   static_assert(RSA % 4 == 0 && BSA % 4 == 0, "float4 spans");
   const f4 z{0.f, 0.f, 0.f, 0.f};
   const int r0 = E.jr * E.nj * (RSA / 4);
-  const int ns4 = act ? r0 + 4 * placed_of_plan(E) * (RSA / 4) : 0;
+  const int ns4 = act ? r0 + 4 * E.live()[2] * (RSA / 4) : 0;
   for (int i = r0 + tm.tl; i < ns4; i += tm.ts) st4(E.rowA(0) + 4 * i, z);
   // the world slot's adjoint is a sink of the sweeps: cleared every step so
   // that it stays finite (it only ever meets zero inverse masses)
@@ -2491,9 +2489,7 @@ SHD void contact_rev_visit(ContactRev& k, ContactRec& h, const DevModel& M, cons
   E.bodyA(c.b)[AIM] += imB;
 }
 // The first nr of a constraint's records in a sweep, and its start impulses
-// (in its row slots).  Two functions, so that the records' loads stay global
-// ones: a choice between the two sources makes flat loads, for which every
-// later wait for LDS waits too.
+// (in its row slots).
 template <int NR>
 SHD void records(float* l, int nr, int s, const float* H) {
 #pragma unroll
@@ -2634,17 +2630,20 @@ SHD void a_pgs_listed(const Team& tm, const DevModel& M, const Env& E, bool act,
     sw.advance(vn, p2);
   }
 }
-template <bool GH, class Team>
+// The sweeps' reverse with a hinge's rows and accumulators in its lanes'
+// registers, the history in global memory.  Contacts' rows stay in LDS: with
+// them in registers too the kernel spilled (ground contacts held: spheres over
+// a floor 13.05 ms per call, else 12.98; arms 14.01 and 13.96).
+template <class Team>
 SHD void a_pgs_held(const Team& tm, const DevModel& M, const Env& E, bool act, const float* gh, float& gmu) {
   const float mu = E.misc()[MISC_MU];
   const Held h = held_of(tm, E, act);
   const bool gnd = h.vc.y == E.nb;
-  auto hist = [&](int it) { return (GH ? gh : E.hist(0)) + (long)it * E.nslot; };   // sweep it's records
+  auto hist = [&](int it) { return gh + (long)it * E.nslot; };   // sweep it's records
   // Each lane reads its own constraints' records: the current sweep's and
   // the previous one's are at hand at a visit, and the one before those is
   // loaded a whole sweep before it is used.
   HingeRev hr;
-  ContactRev cr;         // a ground contact's rows; a pair's stay in LDS
   ContactRec hc;
   float hn[6], hnn[6], cn[3], cnn[3];   // the previous sweep's records, and those of the one before it
   float lt5 = 0.f;
@@ -2659,7 +2658,6 @@ SHD void a_pgs_held(const Team& tm, const DevModel& M, const Env& E, bool act, c
     for (int q = 0; q < 5; ++q) hr.c[q].lt = l[q];
     if (E.jr == 6) lt5 = l[5];
   }
-  if (h.gc >= 0 && gnd) contact_rev_load<false>(cr, E, h.vc.x, h.vc.y, h.vc.z);
   if (h.gc >= 0 && n > 0) {
     records<3>(hc.lt, 3, h.vc.x, hist(n - 1));
     if (n >= 2) records<3>(cn, 3, h.vc.x, hist(n - 2));
@@ -2672,7 +2670,7 @@ SHD void a_pgs_held(const Team& tm, const DevModel& M, const Env& E, bool act, c
     for (int g = nv - 1; g >= 0; --g) {
       if (g == h.gc) {
         if (it == 0) start_impulses<3>(cn, 3, E, h.vc.x);
-        if (gnd) contact_rev_visit<false>(cr, hc, M, E, mu, cn, it == 0, gmu);
+        if (gnd) contact_rev_lds<false>(hc, M, E, h.vc.x, h.vc.y, h.vc.z, mu, cn, it == 0, gmu);
         else contact_rev_lds<true>(hc, M, E, h.vc.x, h.vc.y, h.vc.z, mu, cn, it == 0, gmu);
         for (int q = 0; q < 3; ++q) cn[q] = cnn[q];
         if (it >= 3) records<3>(cnn, 3, h.vc.x, hist(it - 3));
@@ -2693,13 +2691,14 @@ SHD void a_pgs_held(const Team& tm, const DevModel& M, const Env& E, bool act, c
     }
   }
   if (h.gh >= 0) hinge_rev_store(hr, E);
-  if (h.gc >= 0 && gnd) contact_rev_store(cr, E);
   tm.sync();
 }
 template <bool GH, class Team>
 SHD void a_pgs(const Team& tm, const DevModel& M, const Env& E, bool act, const float* gh = nullptr) {
   float gmu = 0.f;
-  if (lanes_hold_rows(tm, E, act)) a_pgs_held<GH>(tm, M, E, act, gh, gmu);
+  // (replays, whose history is in LDS, walk the list: their reverse is the
+  // mode for little memory, and the kernel is as large as it should get)
+  if (GH && lanes_hold_rows(tm, E, act)) a_pgs_held(tm, M, E, act, gh, gmu);
   else a_pgs_listed<GH>(tm, M, E, act, gh, gmu);
   // friction coefficient adjoint (one lane per team holds it after a reduction)
   float tot = tm.team_sum(gmu);
@@ -3187,7 +3186,7 @@ SHD void a_predict_torques(const Team& tm, const DevModel& M, const Env& E, bool
       if (a >= 0) { wrel = wrel - ld3(E.bodyA(a) + AW0); tqd = tqd - ld3(E.bodyA(a) + ATQ); }
       const float dmp = C[JD];
       const bool servo = E.jr == 6;
-      const float tau = (servo ? 0.f : C[JU]) - dmp * dot(wrel, n);
+      const float tau = (servo ? 0.f : E.ctl()[j]) - dmp * dot(wrel, n);
       const float taub = dot(n, tqd);
       f3 nb_ = tau * tqd - (taub * dmp) * wrel;
       // the control's adjoint: the torque's, or a servo's through the target
