@@ -209,7 +209,7 @@ __device__ __forceinline__ void setup_shared(TeamGPU& tm, const DevModel& M, flo
   tm.H2 = tm.H1 + 16 * WSN_SH;
   tm.cnt = reinterpret_cast<int*>(sh + WSN_NET_FLOATS + WSN_TILE_FLOATS);
   tm.map = tm.cnt + 64;
-  wsn_stage(M.wsn, tm.net, threadIdx.x, 64);
+  wsn_stage(M.wsn, tm.net, threadIdx.x);
   __syncthreads();
 }
 

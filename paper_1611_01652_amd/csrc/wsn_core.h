@@ -66,26 +66,45 @@ __device__ __forceinline__ WsnNet wsn_net_at(float* p) {
   return n;
 }
 
-// Copy the packed bfloat16 parameters (global) into the LDS image; threads
-// tid = 0..nt-1 of the workgroup share the work.  Caller synchronises.
-__device__ inline void wsn_stage(const uint16_t* __restrict__ g, const WsnNet& n, int tid, int nt) {
-  for (int i = tid; i < 64 * WSN_S1; i += nt) {
-    const int h = i / WSN_S1, k = i % WSN_S1;
-    n.W1[i] = k < WSN_IN ? g[WSN_W1 + h * WSN_IN + k] : (uint16_t)0;
+// Eight packed parameters in one load (the parameters need only their own
+// two-byte alignment).
+struct __attribute__((packed, aligned(2))) wsn8 { uint16_t v[8]; };
+
+// Copy the packed bfloat16 parameters (global) into the LDS image, and W2's
+// transpose to W2T ([64][WSN_SH]) where it is wanted.  One wave: all of a
+// lane's loads (16 bytes each) are issued before the first is used, then the
+// padding is cleared and the values are placed.  Caller synchronises.
+__device__ inline void wsn_stage(const uint16_t* __restrict__ g, const WsnNet& n, int lane,
+                                 uint16_t* W2T = nullptr) {
+  const wsn8* q = reinterpret_cast<const wsn8*>(g);
+  wsn8 w2[8], w1{}, w3{};
+  for (int u = 0; u < 8; ++u) w2[u] = q[WSN_W2 / 8 + 64 * u + lane];
+  if (lane < WSN_HID * WSN_IN / 8) w1 = q[WSN_W1 / 8 + lane];
+  if (lane < WSN_OUT * WSN_HID / 8) w3 = q[WSN_W3 / 8 + lane];
+  const uint16_t b1 = g[WSN_B1 + lane], b2 = g[WSN_B2 + lane], b3 = lane < WSN_OUT ? g[WSN_B3 + lane] : (uint16_t)0;
+  uint2* z1 = reinterpret_cast<uint2*>(n.W1);
+  for (int i = lane; i < 64 * WSN_S1 / 4; i += 64) z1[i] = make_uint2(0u, 0u);
+  uint2* z3 = reinterpret_cast<uint2*>(n.W3);
+  for (int i = lane; i < 16 * WSN_SH / 4; i += 64) z3[i] = make_uint2(0u, 0u);
+  __syncthreads();
+  for (int u = 0; u < 8; ++u) {
+    const int c = 64 * u + lane, h = c >> 3, k = 8 * (c & 7);
+    uint16_t* d = n.W2 + h * WSN_SH + k;
+    for (int j = 0; j < 8; j += 2)
+      *reinterpret_cast<uint32_t*>(d + j) = (uint32_t)w2[u].v[j] | ((uint32_t)w2[u].v[j + 1] << 16);
+    if (W2T)
+      for (int j = 0; j < 8; ++j) W2T[(k + j) * WSN_SH + h] = w2[u].v[j];
   }
-  for (int i = tid; i < 64 * WSN_SH; i += nt) {
-    const int h = i / WSN_SH, k = i % WSN_SH;
-    n.W2[i] = k < 64 ? g[WSN_W2 + h * 64 + k] : (uint16_t)0;
-  }
-  for (int i = tid; i < 16 * WSN_SH; i += nt) {
-    const int o = i / WSN_SH, k = i % WSN_SH;
-    n.W3[i] = (o < WSN_OUT && k < 64) ? g[WSN_W3 + o * 64 + k] : (uint16_t)0;
-  }
-  for (int i = tid; i < 64; i += nt) {
-    n.b1[i] = bf2f(g[WSN_B1 + i]);
-    n.b2[i] = bf2f(g[WSN_B2 + i]);
-  }
-  for (int i = tid; i < 16; i += nt) n.b3[i] = i < WSN_OUT ? bf2f(g[WSN_B3 + i]) : 0.f;
+  if (lane < WSN_HID * WSN_IN / 8)
+    for (int j = 0; j < 8; ++j) {
+      const int e = 8 * lane + j, h = e / WSN_IN;
+      n.W1[h * WSN_S1 + e - h * WSN_IN] = w1.v[j];
+    }
+  if (lane < WSN_OUT * WSN_HID / 8)
+    for (int j = 0; j < 8; ++j) n.W3[(lane >> 3) * WSN_SH + 8 * (lane & 7) + j] = w3.v[j];
+  n.b1[lane] = bf2f(b1);
+  n.b2[lane] = bf2f(b2);
+  if (lane < 16) n.b3[lane] = bf2f(b3);
 }
 
 // A operand of the input layer: this lane's row (row l % 16) as bfloat16,
@@ -101,10 +120,11 @@ __device__ __forceinline__ bf16x4 wsn_input_operand(const float* xrow, int lane)
 }
 
 // Hidden layer: H[16][64] (bf16, row stride WSN_SH) = relu(A W^T + b), with
-// the A operand fragments given for the 16-wide k blocks.
+// the A operand fragments given for the 16-wide k blocks; HT: also transposed
+// ([64][tstride], the lane's four rows in one store).
 template <int KB>
 __device__ __forceinline__ void wsn_hidden(const bf16x4 (&a)[KB], const uint16_t* W, int wstride, const float* b,
-                                           uint16_t* H, int lane) {
+                                           uint16_t* H, int lane, uint16_t* HT = nullptr, int tstride = 0) {
   const int kq = 4 * (lane >> 4), c16 = lane & 15;
   for (int ct = 0; ct < 4; ++ct) {
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -112,7 +132,12 @@ __device__ __forceinline__ void wsn_hidden(const bf16x4 (&a)[KB], const uint16_t
     for (int ks = 0; ks < KB; ++ks) acc = mfma16(a[ks], ld_bf4(wr + 16 * ks), acc);
     const int col = 16 * ct + c16;
     const float bb = b[col];
-    for (int r = 0; r < 4; ++r) H[(kq + r) * WSN_SH + col] = f2bf(fmaxf(acc[r] + bb, 0.f));
+    bf16x4 h;
+    for (int r = 0; r < 4; ++r) {
+      h[r] = (short)f2bf(fmaxf(acc[r] + bb, 0.f));
+      H[(kq + r) * WSN_SH + col] = (uint16_t)h[r];
+    }
+    if (HT) *reinterpret_cast<bf16x4*>(HT + col * tstride + kq) = h;
   }
 }
 

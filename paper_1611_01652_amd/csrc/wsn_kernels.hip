@@ -64,20 +64,47 @@ __device__ __forceinline__ float col_sum(floatx4 d) {
   return s;
 }
 
+// A lane's share of one 16-record tile, loaded a tile ahead (the first one
+// before the weights are staged): the input layer's operand x (features
+// kq .. kq + 3 of record l % 16), the same tile transposed with the ones
+// column (input l % 16 of records kq .. kq + 3), and the target of output
+// l % 16 of those records.  Zero beyond the inputs and the records.
+struct WsnTileIn { float x[4], xt[4], t[4]; };
+__device__ __forceinline__ WsnTileIn wsn_tile_in(const float* __restrict__ rec, long long stride, long long n,
+                                                 long long tile, int relative, int lane) {
+  const int kq = 4 * (lane >> 4), c16 = lane & 15;
+  const long long r0 = tile * 16, my = r0 + c16;
+  WsnTileIn v;
+  for (int j = 0; j < 4; ++j) {
+    const long long s = r0 + kq + j;
+    const float* q = rec + s * stride;
+    v.x[j] = my < n && kq + j < WSN_IN ? rec[my * stride + kq + j] : 0.f;
+    v.xt[j] = s < n ? (c16 < WSN_IN ? q[c16] : (c16 == WSN_IN ? 1.f : 0.f)) : 0.f;
+    v.t[j] = s < n && c16 < WSN_OUT ? q[WSN_IN + c16] - (relative ? q[4 + c16] : 0.f) : 0.f;
+  }
+  return v;
+}
+
+// Bound by latency: a minibatch of a few thousand records is one tile per
+// workgroup, so the kernel is one pass of staging, two layers forward and
+// back.  Loads are issued together ahead of it, and every transposed tile is
+// written as the lane's four consecutive records in one store (4096 records:
+// 13.7 us; weights staged two bytes at a time and tiles transposed in a
+// second pass 44 us).
 __global__ __launch_bounds__(64) void k_wsn_loss_grad(const uint16_t* __restrict__ w, const float* __restrict__ rec,
                                                       long long stride, long long n, float inv_n, float huber,
                                                       int relative, float* __restrict__ partial) {
   extern __shared__ float lds[];
   const WsnTrainLds L = wsn_train_at(lds);
   const int lane = threadIdx.x, kq = 4 * (lane >> 4), c16 = lane & 15;
-  wsn_stage(w, L.net, lane, 64);
-  for (int i = lane; i < 64 * WSN_ST; i += 64) {
-    const int h = i / WSN_ST, o = i % WSN_ST;
-    L.W3T[i] = o < WSN_OUT ? w[WSN_W3 + o * 64 + h] : (uint16_t)0;
-  }
-  for (int i = lane; i < 64 * WSN_SH; i += 64) {
-    const int a = i / WSN_SH, b = i % WSN_SH;
-    L.W2T[i] = b < 64 ? w[WSN_W2 + b * 64 + a] : (uint16_t)0;
+  const long long n_tiles = (n + 15) / 16;
+  WsnTileIn in = wsn_tile_in(rec, stride, n, blockIdx.x, relative, lane);
+  wsn_stage(w, L.net, lane, L.W2T);
+  __syncthreads();
+  for (int o = 0; o < 16; o += 4) {   // W3T[h][o], h = lane, zero for o >= WSN_OUT
+    bf16x4 t;
+    for (int j = 0; j < 4; ++j) t[j] = (short)L.net.W3[(o + j) * WSN_SH + lane];
+    *reinterpret_cast<bf16x4*>(L.W3T + lane * WSN_ST + o) = t;
   }
   __syncthreads();
   floatx4 g1[4], g2[4][4], g3[4];
@@ -87,34 +114,24 @@ __global__ __launch_bounds__(64) void k_wsn_loss_grad(const uint16_t* __restrict
     for (int j = 0; j < 4; ++j) g2[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
   float gb2[4] = {0.f, 0.f, 0.f, 0.f}, gb3 = 0.f, loss = 0.f;
-  const long long n_tiles = (n + 15) / 16;
   for (long long tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
     const long long r0 = tile * 16;
+    const WsnTileIn ti = in;
+    if (tile + gridDim.x < n_tiles) in = wsn_tile_in(rec, stride, n, tile + gridDim.x, relative, lane);
     // inputs: A operand of row l % 16, and the transposed copy with the ones column
-    const long long my = r0 + c16;
-    const float* xrow = my < n ? rec + my * stride : nullptr;
-    bf16x4 a0[1] = {wsn_input_operand(xrow, lane)};
-    {
-      const int k = lane & 15, s0 = 4 * (lane >> 4);   // input k, records s0..s0+3
-      for (int j = 0; j < 4; ++j) {
-        const long long s = r0 + s0 + j;
-        float v = 0.f;
-        if (s < n) v = k < WSN_IN ? rec[s * stride + k] : (k == WSN_IN ? 1.f : 0.f);
-        L.XT[k * WSN_ST + s0 + j] = f2bf(v);
-      }
+    bf16x4 a0[1], xt;
+    for (int j = 0; j < 4; ++j) {
+      a0[0][j] = (short)f2bf(ti.x[j]);
+      xt[j] = (short)f2bf(ti.xt[j]);
     }
+    *reinterpret_cast<bf16x4*>(L.XT + c16 * WSN_ST + kq) = xt;
     // forward
-    wsn_hidden<1>(a0, L.net.W1, WSN_S1, L.net.b1, L.H1, lane);
+    wsn_hidden<1>(a0, L.net.W1, WSN_S1, L.net.b1, L.H1, lane, L.H1T, WSN_ST);
     __syncthreads();
     bf16x4 a[4];
     wsn_tile_operands(L.H1, lane, a);
-    wsn_hidden<4>(a, L.net.W2, WSN_SH, L.net.b2, L.H2, lane);
+    wsn_hidden<4>(a, L.net.W2, WSN_SH, L.net.b2, L.H2, lane, L.H2T, WSN_ST);
     __syncthreads();
-    for (int i = lane; i < 16 * 64; i += 64) {   // transposed hidden tiles
-      const int s = i / 64, h = i % 64;
-      L.H1T[h * WSN_ST + s] = L.H1[s * WSN_SH + h];
-      L.H2T[h * WSN_ST + s] = L.H2[s * WSN_SH + h];
-    }
     wsn_tile_operands(L.H2, lane, a);
     floatx4 y = {0.f, 0.f, 0.f, 0.f};
     {
@@ -123,13 +140,12 @@ __global__ __launch_bounds__(64) void k_wsn_loss_grad(const uint16_t* __restrict
     }
     // loss and output adjoint (rows kq + r, column c16)
     floatx4 dy;
+    bf16x4 dyb;
     for (int r = 0; r < 4; ++r) {
       const long long s = r0 + kq + r;
       float d = 0.f;
       if (s < n && c16 < WSN_OUT) {
-        const float* q = rec + s * stride;
-        const float t = q[WSN_IN + c16] - (relative ? q[4 + c16] : 0.f);
-        const float e = y[r] + L.net.b3[c16] - t;
+        const float e = y[r] + L.net.b3[c16] - ti.t[r];
         if (huber > 0.f && fabsf(e) > huber) {
           loss += 2.f * huber * fabsf(e) - huber * huber;
           d = 2.f * copysignf(huber, e) * inv_n;
@@ -139,10 +155,10 @@ __global__ __launch_bounds__(64) void k_wsn_loss_grad(const uint16_t* __restrict
         }
       }
       dy[r] = d;
-      const uint16_t hb = f2bf(d);
-      L.DY[(kq + r) * WSN_ST + c16] = hb;
-      L.DYT[c16 * WSN_ST + kq + r] = hb;
+      dyb[r] = (short)f2bf(d);
+      L.DY[(kq + r) * WSN_ST + c16] = (uint16_t)dyb[r];
     }
+    *reinterpret_cast<bf16x4*>(L.DYT + c16 * WSN_ST + kq) = dyb;
     gb3 += col_sum(dy);
     __syncthreads();
     // gW3 += dY^T H2 (rows: outputs, columns: hidden units, k: records)
@@ -157,12 +173,14 @@ __global__ __launch_bounds__(64) void k_wsn_loss_grad(const uint16_t* __restrict
         floatx4 z = {0.f, 0.f, 0.f, 0.f};
         z = mfma16(ad, ld_bf4(L.W3T + (16 * ct + c16) * WSN_ST + kq), z);
         const int col = 16 * ct + c16;
+        const bf16x4 h = ld_bf4(L.H2T + col * WSN_ST + kq);
+        bf16x4 zb;
         for (int r = 0; r < 4; ++r) {
-          if (!(bf2f(L.H2[(kq + r) * WSN_SH + col]) > 0.f)) z[r] = 0.f;
-          const uint16_t hb = f2bf(z[r]);
-          L.DZ2[(kq + r) * WSN_SH + col] = hb;
-          L.DZ2T[col * WSN_ST + kq + r] = hb;
+          if (!(bf2f((uint16_t)h[r]) > 0.f)) z[r] = 0.f;
+          zb[r] = (short)f2bf(z[r]);
+          L.DZ2[(kq + r) * WSN_SH + col] = (uint16_t)zb[r];
         }
+        *reinterpret_cast<bf16x4*>(L.DZ2T + col * WSN_ST + kq) = zb;
         gb2[ct] += col_sum(z);
       }
     }
@@ -180,10 +198,13 @@ __global__ __launch_bounds__(64) void k_wsn_loss_grad(const uint16_t* __restrict
       const uint16_t* wr = L.W2T + (16 * ct + c16) * WSN_SH + kq;
       for (int ks = 0; ks < 4; ++ks) z = mfma16(a[ks], ld_bf4(wr + 16 * ks), z);
       const int col = 16 * ct + c16;
+      const bf16x4 h = ld_bf4(L.H1T + col * WSN_ST + kq);
+      bf16x4 zb;
       for (int r = 0; r < 4; ++r) {
-        if (!(bf2f(L.H1[(kq + r) * WSN_SH + col]) > 0.f)) z[r] = 0.f;
-        L.DZ1T[col * WSN_ST + kq + r] = f2bf(z[r]);
+        if (!(bf2f((uint16_t)h[r]) > 0.f)) z[r] = 0.f;
+        zb[r] = (short)f2bf(z[r]);
       }
+      *reinterpret_cast<bf16x4*>(L.DZ1T + col * WSN_ST + kq) = zb;
     }
     __syncthreads();
     // gW1 (+ gb1 in input column 7) += dZ1^T [X 1]
@@ -212,12 +233,30 @@ __global__ __launch_bounds__(64) void k_wsn_loss_grad(const uint16_t* __restrict
   if (lane == 0) out[WSN_PARAMS] = loss * inv_n;
 }
 
-__global__ void k_wsn_reduce(const float* __restrict__ partial, int n_parts, float* __restrict__ grad,
-                             float* __restrict__ loss) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p > WSN_PARAMS) return;
+// Sum of the workgroups' partials, in a fixed order: a block takes 64
+// parameters, its 16 waves every 16th partial with REDUCE_BATCH loads in
+// flight, and the waves' sums are added in order.  (One thread per parameter
+// summing all partials in turn, on 20 blocks, took 61 us for 256 partials.)
+enum { REDUCE_WAVES = 16, REDUCE_BATCH = 8 };
+__global__ __launch_bounds__(64 * REDUCE_WAVES) void k_wsn_reduce(const float* __restrict__ partial, int n_parts,
+                                                                  float* __restrict__ grad,
+                                                                  float* __restrict__ loss) {
+  __shared__ float sh[REDUCE_WAVES][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, p = blockIdx.x * 64 + lane;
   float s = 0.f;
-  for (int i = 0; i < n_parts; ++i) s += partial[(size_t)i * (WSN_PARAMS + 1) + p];
+  for (int i0 = wv; i0 < n_parts; i0 += REDUCE_WAVES * REDUCE_BATCH) {
+    float v[REDUCE_BATCH];
+    for (int u = 0; u < REDUCE_BATCH; ++u) {
+      const int i = i0 + REDUCE_WAVES * u;
+      v[u] = i < n_parts && p <= WSN_PARAMS ? partial[(size_t)i * (WSN_PARAMS + 1) + p] : 0.f;
+    }
+    s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+  }
+  sh[wv][lane] = s;
+  __syncthreads();
+  if (wv != 0 || p > WSN_PARAMS) return;
+  s = 0.f;
+  for (int w = 0; w < REDUCE_WAVES; ++w) s += sh[w][lane];
   if (p < WSN_PARAMS) {
     if (grad) grad[p] = s;
   } else if (loss) {
@@ -232,7 +271,7 @@ __global__ __launch_bounds__(64) void k_wsn_forward(const uint16_t* __restrict__
   uint16_t* H1 = reinterpret_cast<uint16_t*>(lds + WSN_NET_FLOATS);
   uint16_t* H2 = H1 + 16 * WSN_SH;
   const int lane = threadIdx.x, kq = 4 * (lane >> 4), c16 = lane & 15;
-  wsn_stage(w, net, lane, 64);
+  wsn_stage(w, net, lane);
   __syncthreads();
   const long long n_tiles = (n + 15) / 16;
   for (long long tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
@@ -349,7 +388,7 @@ hipError_t launch_wsn_loss_grad(const uint16_t* w, const float* rec, long long s
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_wsn_reduce, dim3((WSN_PARAMS + 1 + 255) / 256), dim3(256), 0, st, partial,
+  hipLaunchKernelGGL(k_wsn_reduce, dim3((WSN_PARAMS + 1 + 63) / 64), dim3(64 * REDUCE_WAVES), 0, st, partial,
                      n > 0 ? n_parts : 0, grad, loss);
   return hipGetLastError();
 }
