@@ -40,37 +40,66 @@ __device__ __forceinline__ int wrapi(int k, int n) {
   return m < 0 ? m + n : m;
 }
 
+// Texels a and a + 1 (wrapped) of a texture row of n >= 2, in one 8-byte load
+// but at the wrap: a wave's texel loads go to up to 64 cache lines each, and
+// their number bounds k_render.
+struct alignas(4) texel2 { float x, y; };
+__device__ __forceinline__ void texel_pair(const float* row, int a, int n, float* t0, float* t1) {
+  const int am = a < n - 1 ? a : n - 2;
+  const texel2 p = *reinterpret_cast<const texel2*>(row + am);
+  *t0 = p.x;
+  *t1 = p.y;
+  if (am != a) {
+    *t0 = p.y;
+    *t1 = row[0];
+  }
+}
+
 // bilinear sample and its slopes in the texel coordinates
 __device__ __forceinline__ float bilinear(const float* T, int nx, int ny, float u, float v, float* du, float* dv) {
   const float fu0 = floorf(u), fv0 = floorf(v);
   const float fu = u - fu0, fv = v - fv0;
-  const int a0 = wrapi((int)fu0, nx), a1 = wrapi((int)fu0 + 1, nx);
+  const int a0 = wrapi((int)fu0, nx);
   const int b0 = wrapi((int)fv0, ny), b1 = wrapi((int)fv0 + 1, ny);
-  const float t00 = T[b0 * nx + a0], t10 = T[b0 * nx + a1], t01 = T[b1 * nx + a0], t11 = T[b1 * nx + a1];
+  float t00, t10, t01, t11;
+  texel_pair(T + b0 * nx, a0, nx, &t00, &t10);
+  texel_pair(T + b1 * nx, a0, nx, &t01, &t11);
   if (du) *du = (1.f - fv) * (t10 - t00) + fv * (t11 - t01);
   if (dv) *dv = (1.f - fu) * (t01 - t00) + fu * (t11 - t10);
   return (1.f - fu) * (1.f - fv) * t00 + fu * (1.f - fv) * t10 + (1.f - fu) * fv * t01 + fu * fv * t11;
 }
 
-// an integral double's index in [0, n) (fmod is exact at any magnitude)
-__device__ __forceinline__ int wrapd(double k, int n) {
-  double m = fmod(k, (double)n);
+// an integral double's index in [0, n).  Below 2^50 the quotient by a rounded
+// reciprocal is off by at most one, and the remainder is formed exactly (one
+// fused step, a result below 2 n in size); beyond, fmod is exact at any
+// magnitude (its loop per bit of the quotient was a third of k_render).
+__device__ __forceinline__ int wrapd(double k, int n, double inv_n) {
+  double m;
+  if (fabs(k) < 1125899906842624.0) {
+    m = __builtin_fma(-floor(k * inv_n), (double)n, k);
+    if (m >= (double)n) m -= (double)n;
+  } else {
+    m = fmod(k, (double)n);
+  }
   if (m < 0.0) m += (double)n;
   const int r = (int)m;
   return r >= n ? 0 : r;
 }
 
+// reciprocals of the ground's cell and texel counts, formed once per thread
+struct RenderInv { double cell, gnx, gny; };
+
 // the ground's bilinear sample at FP64 texel coordinates (far from the
 // camera they reach hundreds of texels): the floor and the fractions in FP64,
 // the interpolation in FP32
-__device__ __forceinline__ float ground_sample(const RenderTex& tex, double u, double v) {
+__device__ __forceinline__ float ground_sample(const RenderTex& tex, const RenderInv& inv, double u, double v) {
   const double fu0 = floor(u), fv0 = floor(v);
   const float fu = (float)(u - fu0), fv = (float)(v - fv0);
-  const int a0 = wrapd(fu0, tex.gnx), a1 = (a0 + 1) % tex.gnx;
-  const int b0 = wrapd(fv0, tex.gny), b1 = (b0 + 1) % tex.gny;
-  const float* T = tex.ground;
-  const float t00 = T[b0 * tex.gnx + a0], t10 = T[b0 * tex.gnx + a1], t01 = T[b1 * tex.gnx + a0],
-              t11 = T[b1 * tex.gnx + a1];
+  const int a0 = wrapd(fu0, tex.gnx, inv.gnx);
+  const int b0 = wrapd(fv0, tex.gny, inv.gny), b1 = b0 + 1 == tex.gny ? 0 : b0 + 1;
+  float t00, t10, t01, t11;
+  texel_pair(tex.ground + b0 * tex.gnx, a0, tex.gnx, &t00, &t10);
+  texel_pair(tex.ground + b1 * tex.gnx, a0, tex.gnx, &t01, &t11);
   return (1.f - fu) * (1.f - fv) * t00 + fu * (1.f - fv) * t10 + (1.f - fu) * fv * t01 + fu * fv * t11;
 }
 
@@ -125,10 +154,13 @@ __device__ __forceinline__ void stage_spheres(const RenderScene& sc, const float
 // the ray from the centre, m + t0 d, is formed first, so D does not come
 // from the difference of two terms of the size |m|^2 |d|^2 (which loses
 // every digit of a small D in FP32).  Both quotients by a use one
-// reciprocal of a per pixel (ia).  The staged spheres are tested in env
-// order (index k0 + k); the first of equal nearest roots is kept.
-__device__ __forceinline__ void trace_spheres(const float4* cs, int n, int k0, const Ray& ray, float ia, RHit& h) {
-  for (int k = 0; k < n; ++k) {
+// reciprocal of a per pixel (ia).  Of the staged spheres those in the mask
+// (the same in every lane) are tested, in env order (index k0 + bit); the
+// first of equal nearest roots is kept.
+__device__ __forceinline__ void trace_spheres(const float4* cs, unsigned long long mask, int k0, const Ray& ray,
+                                              float ia, RHit& h) {
+  for (; mask; mask &= mask - 1) {
+    const int k = __ffsll(mask) - 1;
     const float4 cc = cs[k];
     const float m0 = ray.c[0] - cc.x, m1 = ray.c[1] - cc.y, m2 = ray.c[2] - cc.z;
     const float t0 = -(ray.d[0] * m0 + ray.d[1] * m1 + ray.d[2] * m2) * ia;
@@ -139,6 +171,49 @@ __device__ __forceinline__ void trace_spheres(const float4* cs, int n, int k0, c
     const float s = t0 - sq >= 1.f ? t0 - sq : t0 + sq;
     if (s >= 1.f && s < h.s) { h.s = s; h.k = k0 + k; }
   }
+}
+
+// A wave's pixels: tiles of kTileW x kTileH, lane l at column l % kTileW, row
+// l / kTileW (64-byte runs of an image row).  Few of an env's spheres are in
+// sight of so small a tile, so a wave first tests the staged spheres against
+// the tile, one per lane, and traces only those left.
+constexpr int kTileW = 16, kTileH = 4;
+static_assert(kTileW * kTileH == 64, "a tile is a wave");
+__device__ __forceinline__ int tiles_x(const RenderCam& cam) { return (cam.width + kTileW - 1) / kTileW; }
+__device__ __forceinline__ int tiles_of(const RenderCam& cam) {
+  return tiles_x(cam) * ((cam.height + kTileH - 1) / kTileH);
+}
+// Every ray of the tile has |d - dc| <= rho for the tile's centre ray dc and
+// rho = half the pixel span along u and v (the triangle inequality: nothing
+// is asked of the axes), so a hit at some s >= 1 needs |s dc - m| <= r + s rho
+// for m = c - C: f(s) = A s^2 - 2 q s + g <= 0 with A = |dc|^2 - rho^2, q =
+// dc . m + r rho, g = |m|^2 - r^2.  A sphere is left out when f has no root,
+// or none that is positive, by margins (1e-5 of the terms) far above the FP32
+// rounding here and in trace_spheres; anything not finite is kept.
+__device__ __forceinline__ unsigned long long tile_spheres(const float4* cs, int n, const RenderCam& cam, int i0,
+                                                           int j0, int lane) {
+  bool keep = false;
+  if (lane < n) {
+    const float u = ((float)(i0 + kTileW / 2) - 0.5f * (float)cam.width) * cam.pitch;
+    const float v = (0.5f * (float)cam.height - (float)(j0 + kTileH / 2)) * cam.pitch;
+    float ex = 0.f, ey = 0.f, a = 0.f, b = 0.f, m2 = 0.f;
+    const float4 cc = cs[lane];
+    const float c[3] = {cc.x, cc.y, cc.z};
+    for (int k = 0; k < 3; ++k) {
+      const float d = cam.focal * cam.axes[6 + k] + u * cam.axes[k] + v * cam.axes[3 + k], m = c[k] - cam.pos[k];
+      ex += cam.axes[k] * cam.axes[k];
+      ey += cam.axes[3 + k] * cam.axes[3 + k];
+      a += d * d;
+      b += d * m;
+      m2 += m * m;
+    }
+    const float rho = 1.001f * cam.pitch * (0.5f * kTileW * sqrtf(ex) + 0.5f * kTileH * sqrtf(ey));
+    const float A = a - rho * rho, q = b + cc.w * rho, g = m2 - cc.w * cc.w;
+    const float disc = q * q - A * g;
+    const bool out = A > 1e-3f * a && (disc < -1e-5f * (q * q + fabsf(A * g)) || (q < 0.f && g > 1e-5f * m2));
+    keep = !out;
+  }
+  return __ballot(keep);
 }
 
 __device__ __forceinline__ void trace_ground(const RenderScene& sc, const Ray& ray, RHit& h) {
@@ -153,100 +228,138 @@ __device__ __forceinline__ float ray_ia(const Ray& ray) {
   return 1.f / (ray.d[0] * ray.d[0] + ray.d[1] * ray.d[1] + ray.d[2] * ray.d[2]);
 }
 
-constexpr int kStage = 64;   // spheres staged in LDS at a time by k_render
+// The colour of a ray: the nearest of its sphere hit and the ground.
+__device__ __forceinline__ float pixel_colour(const RenderScene& sc, const float* x, const Ray& ray,
+                                              const RenderTex& tex, const RenderInv& inv, int s0, RHit h) {
+  trace_ground(sc, ray, h);
+  if (h.k == -1) {
+    const double sg = ground_s(ray);
+    const double gu = ((double)ray.c[0] + sg * ray.d64[0]) * inv.cell;
+    const double gv = ((double)ray.c[1] + sg * ray.d64[1]) * inv.cell;
+    return ground_sample(tex, inv, gu, gv);
+  }
+  if (h.k < 0) return 0.f;
+  const int g = s0 + h.k, b = sc.sph_body[g];
+  const float4 so = sc.sph[g];
+  const float o[3] = {so.x, so.y, so.z};
+  float c[3], q[3];
+  sphere_centre(x, sc.B, b, o, c);
+  for (int k = 0; k < 3; ++k) q[k] = ray.c[k] + h.s * ray.d[k] - c[k];
+  // l = R^T q / r (R row-major at x[3 + 3 r + i])
+  const float lx = (x[3 * sc.B + b] * q[0] + x[6 * sc.B + b] * q[1] + x[9 * sc.B + b] * q[2]) / so.w;
+  const float ly = (x[4 * sc.B + b] * q[0] + x[7 * sc.B + b] * q[1] + x[10 * sc.B + b] * q[2]) / so.w;
+  return bilinear(tex.sphere, tex.snx, tex.sny, (lx + 1.f) * (0.5f * (float)(tex.snx - 1)),
+                  (ly + 1.f) * (0.5f * (float)(tex.sny - 1)), nullptr, nullptr);
+}
 
-// One thread per pixel, a workgroup 256 pixels of one env; the env's spheres
-// are staged kStage at a time (every thread of the workgroup takes part in
-// the staging, so no thread leaves before the last chunk).
+constexpr int kStage = 64;    // spheres staged in LDS at a time by k_render
+constexpr int kTilesPerWave = 8;
+
+// One pixel per lane; a workgroup of four waves takes 4 kTilesPerWave tiles
+// of one env.  An env's spheres are staged once per workgroup (kStage at a
+// time, again for each tile, where it has more).  Bound by instruction issue
+// (the ground's FP64 intersection the largest part) and the texel loads.  512
+// images of 288 x 96 over chains of 2..16 spheres: 98 us, 57 MB written; with
+// every sphere tested per pixel, fmod and four texel loads 153 us.
 __global__ __launch_bounds__(256) void k_render(RenderScene sc, const float* x, RenderCam cam, RenderTex tex,
                                                 float* image) {
   __shared__ float4 cs[kStage];
-  const int e = blockIdx.y;
-  const int n = cam.width * cam.height;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  const bool live = p < n;
-  const Ray ray = pixel_ray(cam, live ? p % cam.width : 0, live ? p / cam.width : 0);
-  const float ia = ray_ia(ray);
-  RHit h{-2, INFINITY};
+  const int e = blockIdx.y, lane = threadIdx.x & 63;
+  const int n = cam.width * cam.height, tx = tiles_x(cam), nt = tiles_of(cam);
   const int s0 = sc.env_sph[e], s1 = sc.env_sph[e + 1];
-  for (int g0 = s0; g0 < s1; g0 += kStage) {
-    const int g1 = g0 + kStage < s1 ? g0 + kStage : s1;
-    __syncthreads();
-    stage_spheres(sc, x, g0, g1, cs);
-    __syncthreads();
-    trace_spheres(cs, g1 - g0, g0 - s0, ray, ia, h);
+  const RenderInv inv{1.0 / (double)tex.cell, 1.0 / (double)tex.gnx, 1.0 / (double)tex.gny};
+  for (int q = 0; q < kTilesPerWave; ++q) {
+    const int tile = (blockIdx.x * kTilesPerWave + q) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i0 = tile % tx * kTileW, j0 = tile / tx * kTileH;
+    const int i = i0 + lane % kTileW, j = j0 + lane / kTileW;
+    const Ray ray = pixel_ray(cam, i, j);
+    RHit h{-2, INFINITY};
+    for (int g0 = s0; g0 < s1; g0 += kStage) {
+      const int g1 = g0 + kStage < s1 ? g0 + kStage : s1;
+      if (q == 0 || s1 - s0 > kStage) {
+        __syncthreads();
+        stage_spheres(sc, x, g0, g1, cs);
+        __syncthreads();
+      }
+      const unsigned long long mask = tile_spheres(cs, g1 - g0, cam, i0, j0, lane);
+      if (mask) trace_spheres(cs, mask, g0 - s0, ray, ray_ia(ray), h);
+    }
+    if (tile < nt && i < cam.width && j < cam.height)
+      image[(size_t)e * n + (size_t)j * cam.width + i] = pixel_colour(sc, x, ray, tex, inv, s0, h);
   }
-  if (!live) return;
-  trace_ground(sc, ray, h);
-  float col = 0.f;
-  if (h.k == -1) {
-    const double sg = ground_s(ray);
-    const double gu = ((double)ray.c[0] + sg * ray.d64[0]) / (double)tex.cell;
-    const double gv = ((double)ray.c[1] + sg * ray.d64[1]) / (double)tex.cell;
-    col = ground_sample(tex, gu, gv);
-  } else if (h.k >= 0) {
-    const int g = s0 + h.k, b = sc.sph_body[g];
-    const float4 so = sc.sph[g];
-    const float o[3] = {so.x, so.y, so.z};
-    float c[3], q[3];
-    sphere_centre(x, sc.B, b, o, c);
-    for (int k = 0; k < 3; ++k) q[k] = ray.c[k] + h.s * ray.d[k] - c[k];
-    // l = R^T q / r (R row-major at x[3 + 3 r + i])
-    const float lx = (x[3 * sc.B + b] * q[0] + x[6 * sc.B + b] * q[1] + x[9 * sc.B + b] * q[2]) / so.w;
-    const float ly = (x[4 * sc.B + b] * q[0] + x[7 * sc.B + b] * q[1] + x[10 * sc.B + b] * q[2]) / so.w;
-    col = bilinear(tex.sphere, tex.snx, tex.sny, (lx + 1.f) * (0.5f * (float)(tex.snx - 1)),
-                   (ly + 1.f) * (0.5f * (float)(tex.sny - 1)), nullptr, nullptr);
-  }
-  image[(size_t)e * n + p] = col;
 }
 
-constexpr int kGradWaves = 4;
+// Sum over the wave's 64 lanes in a fixed order, valid in lane 63 (adds
+// along rows of 16 lanes, then across the rows, without LDS).
+__device__ __forceinline__ float wave_sum63(float v) {
+#define SIM_ADD_DPP(ctrl, rows) \
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, rows, 0xf, true))
+  SIM_ADD_DPP(0x111, 0xf);   // row_shr:1, 2, 4, 8
+  SIM_ADD_DPP(0x112, 0xf);
+  SIM_ADD_DPP(0x114, 0xf);
+  SIM_ADD_DPP(0x118, 0xf);
+  SIM_ADD_DPP(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
+  SIM_ADD_DPP(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+#undef SIM_ADD_DPP
+  return v;
+}
+
+constexpr int kGradWaves = 16;
 constexpr int kGradThreads = 64 * kGradWaves;
 
-// One workgroup of four waves per env.  In each pass the workgroup takes 256
-// consecutive pixels, wave v the v-th 64 of them, one per lane.  A lane whose
-// pixel shows sphere k forms that pixel's 12 terms (the body's position 3,
-// rotation 9); then, for each sphere that some lane of the wave shows (in
-// the order of the lowest such lane), the wave adds those lanes' terms by a
-// butterfly over the 64 lanes (a fixed tree) and lane 0 adds the sums to the
-// wave's row for that sphere in LDS.  At the end the four waves' rows are
+// One workgroup of 16 waves per env (512 images of 288 x 96: 65 us; with four
+// waves, each waiting for its own loads, every pixel traced and the sums by
+// LDS butterflies 310 us).  Wave v takes every
+// 16th tile from the v-th; a tile with no sphere in sight is done at once,
+// its weights unread.  A lane whose pixel shows sphere k forms that pixel's
+// 12 terms (the body's position 3, rotation 9); then, for each sphere that
+// some lane of the wave shows (in the order of the lowest such lane), the
+// wave adds those lanes' terms in a fixed order and lane 63 adds the sums to
+// the wave's row for that sphere in LDS.  At the end the waves' rows are
 // added in wave order and each sphere's sums go to its body, spheres in env
 // order.  Every sum runs in an order fixed by the inputs, so the gradient is
 // bitwise reproducible.
 __global__ __launch_bounds__(kGradThreads) void k_render_grad(RenderScene sc, const float* x, RenderCam cam,
                                                               RenderTex tex, const float* w, float* g_x) {
   __shared__ float4 cs[kRenderMaxSpheres];
+  __shared__ float rot[kRenderMaxSpheres][12];   // body rotation 9, sphere offset 3
   __shared__ float acc[kGradWaves][kRenderMaxSpheres][12];
   __shared__ float tot[kRenderMaxSpheres][12];
-  const int e = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int n = cam.width * cam.height;
+  const int e = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int n = cam.width * cam.height, tx = tiles_x(cam), nt = tiles_of(cam);
   const int s0 = sc.env_sph[e], ns = sc.env_sph[e + 1] - s0;
   for (int u = t; u < kGradWaves * kRenderMaxSpheres * 12; u += kGradThreads) (&acc[0][0][0])[u] = 0.f;
   stage_spheres(sc, x, s0, s0 + ns, cs);
+  for (int u = t; u < ns * 12; u += kGradThreads) {
+    const int k = u / 12, c = u % 12;
+    rot[k][c] = c < 9 ? x[(size_t)(3 + c) * sc.B + sc.sph_body[s0 + k]]
+                      : reinterpret_cast<const float*>(&sc.sph[s0 + k])[c - 9];
+  }
   __syncthreads();
   const float kx = 0.5f * (float)(tex.snx - 1), ky = 0.5f * (float)(tex.sny - 1);
-  for (int base = 0; base < n; base += kGradThreads) {
-    const int p = base + t;
+  for (int tile = wv; tile < nt; tile += kGradWaves) {
+    const int i0 = tile % tx * kTileW, j0 = tile / tx * kTileH;
+    const unsigned long long mask = tile_spheres(cs, ns, cam, i0, j0, lane);
+    if (mask == 0) continue;
+    const int i = i0 + lane % kTileW, j = j0 + lane / kTileW;
     int hk = -1;
     float v[12];
     for (int c = 0; c < 12; ++c) v[c] = 0.f;
-    const float wt = p < n ? w[(size_t)e * n + p] : 0.f;
+    const float wt = i < cam.width && j < cam.height ? w[(size_t)e * n + (size_t)j * cam.width + i] : 0.f;
     if (wt != 0.f) {
-      const Ray ray = pixel_ray(cam, p % cam.width, p / cam.width);
+      const Ray ray = pixel_ray(cam, i, j);
       RHit h{-2, INFINITY};
-      trace_spheres(cs, ns, 0, ray, ray_ia(ray), h);
-      trace_ground(sc, ray, h);
+      trace_spheres(cs, mask, 0, ray, ray_ia(ray), h);
+      if (h.k >= 0) trace_ground(sc, ray, h);
       // the ground and the background do not depend on the state
       if (h.k >= 0) {
         hk = h.k;
-        const int g = s0 + h.k, b = sc.sph_body[g];
-        const float4 so = sc.sph[g];
-        const float o[3] = {so.x, so.y, so.z};
-        const float r = so.w;
         const float4 cc = cs[h.k];
         const float c[3] = {cc.x, cc.y, cc.z};
-        float q[3], R[9];
-        for (int k = 0; k < 9; ++k) R[k] = x[(3 + k) * sc.B + b];
+        const float r = cc.w;
+        float q[3], R[9], o[3];
+        for (int k = 0; k < 9; ++k) R[k] = rot[h.k][k];
+        for (int k = 0; k < 3; ++k) o[k] = rot[h.k][9 + k];
         for (int k = 0; k < 3; ++k) q[k] = ray.c[k] + h.s * ray.d[k] - c[k];
         const float lx = (R[0] * q[0] + R[3] * q[1] + R[6] * q[2]) / r;
         const float ly = (R[1] * q[0] + R[4] * q[1] + R[7] * q[2]) / r;
@@ -279,9 +392,8 @@ __global__ __launch_bounds__(kGradThreads) void k_render_grad(RenderScene sc, co
       const bool mine = hk == kk;
       float r[12];
       for (int c = 0; c < 12; ++c) r[c] = mine ? v[c] : 0.f;
-      for (int m = 32; m >= 1; m >>= 1)
-        for (int c = 0; c < 12; ++c) r[c] += __shfl_xor(r[c], m);
-      if (lane == 0)
+      for (int c = 0; c < 12; ++c) r[c] = wave_sum63(r[c]);
+      if (lane == 63)
         for (int c = 0; c < 12; ++c) acc[wv][kk][c] += r[c];
       todo &= ~__ballot(mine);
     }
@@ -313,7 +425,8 @@ hipError_t launch_render(const RenderScene& sc, const float* x, const RenderCam&
                          float* image, hipStream_t st) {
   const int n = cam.width * cam.height;
   if (sc.E == 0 || n == 0) return hipSuccess;
-  const dim3 grid((n + 255) / 256, sc.E);
+  const int tiles = ((cam.width + kTileW - 1) / kTileW) * ((cam.height + kTileH - 1) / kTileH);
+  const dim3 grid((tiles + 4 * kTilesPerWave - 1) / (4 * kTilesPerWave), sc.E);
   hipLaunchKernelGGL(k_render, grid, dim3(256), 0, st, sc, x, cam, tex, image);
   return hipGetLastError();
 }
