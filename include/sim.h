@@ -410,8 +410,8 @@ sim_status sim_env_buckets(sim_handle h, int32_t* bucket_of_env);
 /* ---- Replayable step sequences (HIP graphs). ----
  * Captures n_steps consecutive sim_step calls into a HIP graph, for callers
  * that step the simulation in a loop (a policy in the loop, serving): one
- * sim_graph_launch then costs one graph launch instead of n_steps x (queue
- * reset + kernel) launches per bucket.  Nothing runs at capture time.
+ * sim_graph_launch then costs one graph launch and one kernel per bucket, with
+ * every env's state kept on chip between its steps.  Nothing runs at capture time.
  *   x: device [2][18][B]; step k reads x[k % 2] and writes x[(k + 1) % 2],
  *      so the result is in x[n_steps % 2].
  *   u: device control tape [n_steps][J] (step k uses row k) or, for

@@ -46,12 +46,14 @@ struct GradArgs {
 
 struct StepArgs {
   const float* x_in;
-  float* x_out;
-  const float* u;      // [J] (null with a controller)
+  float* x_out;        // the state after the last step
+  const float* u;      // [n_steps][J] (null with a controller)
   const float* lam_in;
   float* lam_out;
-  uint32_t* flags;
-  int t;               // step index (clock input of a controller)
+  uint32_t* flags;     // of the last step
+  int t;               // index of the first step (clock input of a controller)
+  int n_steps;
+  float* x_prev;       // several steps: the state before the last one, else null
 };
 
 SHD size_t ckpt_stride(const DevModel& M) { return (size_t)18 * M.B + M.lam_tot; }
@@ -120,16 +122,27 @@ SHD_FLAT void env_rollout(const Team& tm, const DevModel& M, const Env& E, bool 
 }
 
 template <class Team, bool SOLVE = false>
-SHD_FLAT void env_single_step(const Team& tm, const DevModel& M, const Env& E, bool valid, const StepArgs& a) {
+SHD_FLAT void env_steps(const Team& tm, const DevModel& M, const Env& E, bool valid, const StepArgs& a) {
   if (valid) {
     load_env_static(tm, M, E);
     load_state(tm, E, a.x_in, M.B);
     load_ws(tm, E, a.lam_in);
   }
   tm.sync();
-  if (SOLVE) env_step_solve(tm, M, E, a.u, valid, a.t, nullptr);
-  else env_step(tm, M, E, a.u, valid, a.t);
-  tm.sync();
+  // The env's state stays in LDS from step to step, as in a rollout (16 steps
+  // of 256 chains of 2..16 bodies: 1.00 ms; a kernel, a queue reset and a
+  // fork and join of the buckets' streams per step 2.05 ms).
+  for (int k = 0; k < a.n_steps; ++k) {
+    if (k > 0) {
+      if (valid && k == a.n_steps - 1) store_state(tm, E, a.x_prev, M.B);
+      if (valid && tm.tl == 0) *reinterpret_cast<int*>(E.misc() + MISC_FLAGS) = 0;
+      tm.sync();
+    }
+    const float* u = a.u ? a.u + (size_t)k * M.J : nullptr;
+    if (SOLVE) env_step_solve(tm, M, E, u, valid, a.t + k, nullptr);
+    else env_step(tm, M, E, u, valid, a.t + k);
+    tm.sync();
+  }
   uint32_t fl = valid ? nonfinite_flag(tm, E) : 0u;
   if (valid) {
     store_state(tm, E, a.x_out, M.B);

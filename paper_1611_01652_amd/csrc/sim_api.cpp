@@ -191,11 +191,10 @@ int grid_for(const sim_model* h, long long units, long long bytes) {
 }
 int grid_for(const sim_model* h, const Bucket& b, long long bytes) { return grid_for(h, b.n_tiles, bytes); }
 
-// One bucket's kernels (queue reset + launch) on stream sx.
+// One bucket's kernels (queue reset, but for steps, + launch) on stream sx.
 bool bucket_step(sim_model* h, size_t i, const DevModel& M, const StepArgs& a, hipStream_t sx) {
   const Bucket& b = h->buckets[i];
-  TileSet ts{b.envs_dev, b.n_tiles, b.floats_fwd, h->d_queue + i, 1};
-  if (launch_zero(ts.queue, 1, sx) != hipSuccess) return false;
+  TileSet ts{b.envs_dev, b.n_tiles, b.floats_fwd, nullptr, 1};
   const long long lds = fwd_bytes(h, b);
   return launch_step(M, ts, b.team, grid_for(h, b, lds), (size_t)lds, a, sx) == hipSuccess;
 }
@@ -244,9 +243,12 @@ bool prep_controls(sim_model* h, DevModel& M, const float* u, hipStream_t st) {
   return launch_ctrl_transpose(u, h->d_wt, M.mlp_in, M.mlp_h1, M.mlp_h2, M.mlp_out, st) == hipSuccess;
 }
 
+// n_steps steps in one kernel per bucket: an env's steps need nothing of
+// other envs, and its state stays on chip between them.
 sim_status launch_steps(sim_model* h, const float* x_in, float* x_out, const float* u, const float* lam_in,
-                        float* lam_out, int32_t t, uint32_t* env_flags, hipStream_t st) {
-  StepArgs a{x_in, x_out, h->M.ctrl ? nullptr : u, lam_in, lam_out, env_flags, t};
+                        float* lam_out, int32_t t, uint32_t* env_flags, hipStream_t st, int32_t n_steps = 1,
+                        float* x_prev = nullptr) {
+  StepArgs a{x_in, x_out, h->M.ctrl ? nullptr : u, lam_in, lam_out, env_flags, t, n_steps, x_prev};
   DevModel M = h->M;
   if (!prep_controls(h, M, u, st)) return check_device("sim_step controls");
   return run_buckets(h, st, [&](size_t i, hipStream_t sx) { return bucket_step(h, i, M, a, sx); },
@@ -1017,10 +1019,9 @@ sim_status sim_step_graph(sim_handle h, int32_t n_steps, float* x, const float* 
     return check_device("sim_step_graph begin capture");
   }
   const size_t xs = (size_t)18 * M.B;
-  for (int k = 0; k < n_steps && s == SIM_OK; ++k) {
-    const float* uk = M.ctrl ? u : (u ? u + (size_t)k * M.J : nullptr);
-    s = launch_steps(h, x + (k & 1) * xs, x + ((k + 1) & 1) * xs, uk, lam, lam, t0 + k, env_flags, cs);
-  }
+  // (as step by step: the result in x[n_steps % 2], the state before it in the other)
+  s = launch_steps(h, x, x + (n_steps & 1) * xs, u, lam, lam, t0, env_flags, cs, n_steps,
+                   n_steps > 1 ? x + ((n_steps - 1) & 1) * xs : nullptr);
   const hipError_t ec = hipStreamEndCapture(cs, &g->graph);
   (void)hipStreamDestroy(cs);
   if (s != SIM_OK || ec != hipSuccess || hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0) != hipSuccess) {

@@ -263,11 +263,13 @@ __global__ __launch_bounds__(64) void k_step(DevModel M, TileSet ts, StepArgs a)
   setup_shared(tm, M, lds, ts.env_floats, SOLVE != 0);
   const int team = threadIdx.x / TEAM;
   constexpr int EPW = 64 / TEAM;
-  for (int tile = next_tile(ts.queue); tile < ts.n_tiles; tile = next_tile(ts.queue)) {
+  // (the steps of a bucket's tiles cost alike, so the tiles are dealt out in
+  // turn: no queue to reset, which was a launch of its own per bucket)
+  for (int tile = blockIdx.x; tile < ts.n_tiles; tile += gridDim.x) {
     const int ie = ts.envs[tile * EPW + team];
     const bool valid = ie >= 0;
     Env E = make_env(M, valid ? ie : ts.envs[tile * EPW], lds + team * ts.env_floats, M.n_iters, false);
-    env_single_step<TeamGPU, SOLVE != 0>(tm, M, E, valid, a);
+    env_steps<TeamGPU, SOLVE != 0>(tm, M, E, valid, a);
     __syncthreads();
   }
 }

@@ -512,7 +512,9 @@ class Simulator:
         t = self.torch
         xo = t.empty_like(x)
         lo = t.empty_like(lam)
-        flags = t.zeros(max(self.info.n_envs, 1), dtype=t.int32, device="cuda")
+        # (every env's flags are written, so they need no clearing launch of their own)
+        E = self.info.n_envs
+        flags = (t.empty if E else t.zeros)(max(E, 1), dtype=t.int32, device="cuda")
         st = self.lib.sim_step(self.h, _ptr(x), _ptr(xo), _ptr(u), _ptr(lam), _ptr(lo), int(t_index), _ptr(flags),
                                self._stream())
         _check(self.lib, st, "sim_step")
