@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -255,6 +256,77 @@ sim_status launch_steps(sim_model* h, const float* x_in, float* x_out, const flo
                      "sim_step launch");
 }
 
+// Hardware queues HIP spreads a process's streams over.
+int hw_queues() {
+  const char* v = std::getenv("GPU_MAX_HW_QUEUES");
+  const int n = v ? std::atoi(v) : 0;
+  return n > 0 ? n : 4;
+}
+
+// An env class: what the envs of one (team, LDS) class need, and how many.
+struct EnvClass { int team, floats_fwd, floats_adj, ccap, n; };
+
+// Runs of consecutive classes to merge into one bucket each; returns the first
+// class of each run.  Buckets on one hardware queue run one after another,
+// and a bucket lasts at least the latency of its envs' steps, about the same
+// for short and long chains: with more buckets than queues, a model whose
+// envs fit the device at once waits for its queues' turns (2048 chains of
+// 2..32 bodies in 15 buckets on 4 queues: 4 turns of about 10 ms in the
+// reverse, the device mostly idle).  Fewer buckets reserve the largest env's
+// LDS for each of theirs, which costs once the device is full.  So the number
+// of runs is the one with the least max(turns, rounds): turns = runs per
+// queue, rounds = the tiles' share of the device (of a CU the LDS of a
+// tile, or one SIMD), for the split that needs the least of it; at equal
+// estimates the most runs.  On 4 queues, a call of forward and reverse, in
+// buckets of a quarter octave each -> merged: those 2048 chains 58.0 -> 40.8 ms
+// (8 buckets), 333 of them by segments 36.5 -> 9.9 ms (4), a 16-step graph of
+// 256 chains 1.00 -> 0.38 ms (4), a tolerance rollout of 512 7.4 -> 5.2 ms (4).
+// A run whose tile would not fit the LDS is no choice.
+std::vector<int> merge_classes(const DevModel& M, const std::vector<EnvClass>& cl, int n_cu, int max_lds,
+                               int queues) {
+  const int n = (int)cl.size();
+  auto rounds = [&](int a, int b) {   // classes [a, b) as one bucket
+    EnvClass g{0, 0, 0, 0, 0};
+    for (int i = a; i < b; ++i) {
+      g.team = std::max(g.team, cl[i].team);
+      g.floats_fwd = std::max(g.floats_fwd, cl[i].floats_fwd);
+      g.floats_adj = std::max(g.floats_adj, cl[i].floats_adj);
+      g.ccap = std::max(g.ccap, cl[i].ccap);
+      g.n += cl[i].n;
+    }
+    const long long bytes = adj_bytes(M, g.team, g.floats_adj);
+    if (b - a > 1 && std::max(bytes, fwd_bytes(M, g.team, g.floats_fwd, g.ccap)) > max_lds) return 1e30;
+    const int epw = 64 / g.team;
+    const double share = std::max((double)bytes / (double)kLdsPerCu, 1.0 / kSimdsPerCu);
+    return ((g.n + epw - 1) / epw) * share / std::max(n_cu, 1);
+  };
+  // best[k][b]: least rounds of classes [0, b) in k runs; from: the last run's first class
+  std::vector<std::vector<double>> best(n + 1, std::vector<double>(n + 1, 1e300));
+  std::vector<std::vector<int>> from(n + 1, std::vector<int>(n + 1, 0));
+  best[0][0] = 0.0;
+  for (int k = 1; k <= n; ++k)
+    for (int b = k; b <= n; ++b)
+      for (int a = k - 1; a < b; ++a) {
+        const double r = best[k - 1][a] + rounds(a, b);
+        if (r < best[k][b]) {
+          best[k][b] = r;
+          from[k][b] = a;
+        }
+      }
+  int runs = 1;
+  double least = 1e300;
+  for (int k = 1; k <= n; ++k) {
+    const double est = std::max((double)((k + queues - 1) / queues), best[k][n]);
+    if (est <= least) {
+      least = est;
+      runs = k;
+    }
+  }
+  std::vector<int> first(runs);
+  for (int k = runs, b = n; k > 0; b = from[k][b], --k) first[k - 1] = from[k][b];
+  return first;
+}
+
 // Team widths a bucket may use: powers of two from its narrowest whose tile
 // fits the device's LDS.
 std::vector<int> admissible_teams(const sim_model* h, const Bucket& b) {
@@ -447,18 +519,32 @@ sim_status sim_init(const sim_model_desc* d, sim_handle* out) {
     team_of[e] = team;
   }
   M.lam_tot = h->lam_off[E];
-  // buckets by team size and LDS size class (a quarter octave), so a tile
-  // reserves about what its envs need; tiles sorted longest episode first
+  // classes by team size and LDS size (a quarter octave), so a tile reserves
+  // about what its envs need, merged into buckets where they are too many for
+  // the queues; tiles sorted longest episode first
   auto lds_class = [&](int e) { return (int)std::floor(4.0 * std::log2((double)std::max(adj_of[e], 1))); };
   std::vector<std::pair<int, int>> keys;
   for (int e = 0; e < E; ++e) keys.push_back({team_of[e], lds_class(e)});
   std::sort(keys.begin(), keys.end());
   keys.erase(std::unique(keys.begin(), keys.end()), keys.end());
-  for (const auto& key : keys) {
-    const int team = key.first;
+  std::vector<EnvClass> classes(keys.size(), EnvClass{0, 0, 0, 0, 0});
+  std::vector<int> class_of(E);
+  for (int e = 0; e < E; ++e) {
+    const std::pair<int, int> key{team_of[e], lds_class(e)};
+    class_of[e] = (int)(std::lower_bound(keys.begin(), keys.end(), key) - keys.begin());
+    EnvClass& c = classes[class_of[e]];
+    c = EnvClass{team_of[e], std::max(c.floats_fwd, fwd_of[e]), std::max(c.floats_adj, adj_of[e]),
+                 std::max(c.ccap, P.ccap_of[e]), c.n + 1};
+  }
+  std::vector<int> runs;
+  if (!classes.empty()) runs = merge_classes(M, classes, h->n_cu, h->max_lds, hw_queues());
+  for (size_t r = 0; r < runs.size(); ++r) {
+    const int c0 = runs[r], c1 = r + 1 < runs.size() ? runs[r + 1] : (int)classes.size();
+    int team = 0;
+    for (int c = c0; c < c1; ++c) team = std::max(team, classes[c].team);
     std::vector<int> ids;
     for (int e = 0; e < E; ++e)
-      if (team_of[e] == team && lds_class(e) == key.second) ids.push_back(e);
+      if (class_of[e] >= c0 && class_of[e] < c1) ids.push_back(e);
     std::stable_sort(ids.begin(), ids.end(), [&](int a, int b) {
       if (d->T_env[a] != d->T_env[b]) return d->T_env[a] > d->T_env[b];
       return adj_of[a] > adj_of[b];
