@@ -4,8 +4,8 @@ A wave whose envs have at most one joint per pair of lanes and one placed
 contact per lane keeps its constraints' rows in registers; with more contacts
 than lanes it walks the visit list.  Twelve unjointed spheres in a pile place
 more contacts than a team of 8 lanes has, and fewer than one of 64, so the two
-widths take the two paths; chains of 2..5 bodies sit at the narrowest width
-that holds their joints.  The constraint updates are the same, so every result
+widths take the two paths; chains of 2..5 bodies are run at the narrowest width
+that holds their joints and at 64.  The constraint updates are the same, so every result
 has the same bits, but for the friction coefficient's gradient, whose terms
 are summed per lane first: rounding of a sum of n terms, bounded by
 n * 2^-24 of the sum of their magnitudes; it is compared at 1e-5 relative."""
@@ -39,11 +39,11 @@ def test_held_and_listed_sweeps_agree(model, store):
             w.x0[:, 2] -= 0.15
             w.x0 = W.f32(w.x0)
             w.extra = {"grad_store": store}
-        w.min_team = team
+        w.min_team = team   # (1: no wider than the envs need)
         return w
 
     print("case held rows", model, store, flush=True)
-    a, b = gpu_run(make(0)), gpu_run(make(64))
+    a, b = gpu_run(make(1)), gpu_run(make(64))
     assert (a["flags"] == 0).all() and np.abs(a["lam_final"]).max() > 0
     for k in a:
         if k == "g_mu":
