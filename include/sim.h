@@ -251,8 +251,10 @@ const char* sim_last_error(void);
  * joins them back to the caller's stream.  HIP maps streams onto
  * GPU_MAX_HW_QUEUES hardware queues (4 unless the process sets it before HIP
  * starts) and runs the kernels of streams that share a queue one after
- * another: for the buckets to run at once, set it to at least the bucket
- * count (sim_get_teams). */
+ * another.  The envs' size classes are merged into buckets (sim_get_teams) with
+ * that number in view, read when the model is made: a model that fits the
+ * device at once takes about one bucket per queue, one that fills it keeps its
+ * classes, and for these to run at once it should be at least their count. */
 sim_status sim_init(const sim_model_desc* desc, sim_handle* out);
 sim_status sim_destroy(sim_handle h);
 sim_status sim_get_info(sim_handle h, sim_info* info);
@@ -423,7 +425,7 @@ sim_status sim_env_buckets(sim_handle h, int32_t* bucket_of_env);
  *      non-finite state stays non-finite, so it is still flagged).
  * The pointers are baked into the graph: every launch reads and writes the
  * same buffers.  A graph must not run concurrently with another call on the
- * same handle (they share the tile queues).  Release with sim_graph_destroy;
+ * same handle (they share its streams and events).  Release with sim_graph_destroy;
  * while graphs of a handle are alive, sim_destroy, sim_tune and
  * sim_set_teams refuse with SIM_E_STATE (the graphs use its tile lists). */
 typedef struct sim_graph_s* sim_graph;
