@@ -272,8 +272,8 @@ int hw_queues() {
 // has cannot be asked, so it is tried: kernels on the streams chosen so far
 // wait, within a bound, for one on the new stream; if some of them does not see
 // it, the two share a queue (or the device is busy) and another stream is
-// tried, up to 2 x queues in all.  About 0.1 ms per stream when a model of
-// several buckets is made.
+// tried, up to 2 x queues in all: 0.1 to 0.2 ms each, when a model of several
+// buckets is made.
 bool make_streams(sim_model* h, int n, int queues) {
   auto create = [](hipStream_t* s) { return hipStreamCreateWithFlags(s, hipStreamNonBlocking) == hipSuccess; };
   const int want = std::min(n, queues);
@@ -289,11 +289,11 @@ bool make_streams(sim_model* h, int n, int queues) {
     ok = launch_set_flag(flags, first) == hipSuccess && launch_wait_flag(flags, flags + 1, 0, first) == hipSuccess &&
          hipStreamSynchronize(first) == hipSuccess;
   }
-  const long long ticks = 100000;   // 1 ms of the 100 MHz clock
   for (int tries = 1; ok && (int)h->streams.size() < want && tries < 2 * queues + 1; ++tries) {
     hipStream_t s;
     if (!(ok = create(&s))) break;
     const int k = (int)h->streams.size();
+    const long long ticks = 10000 + 2500 * k;   // of the 100 MHz clock: 100 us and 25 us a launch
     ok = launch_zero(flags, k + 1, s) == hipSuccess && hipStreamSynchronize(s) == hipSuccess;
     for (int i = 0; ok && i < k; ++i)
       ok = launch_wait_flag(flags, flags + 1 + i, ticks, h->streams[i]) == hipSuccess;
