@@ -197,6 +197,12 @@ enum { JA_DAMP = 0, JA_DAMPC = 1, JA_ANCP = 2, JA_ANCC = 5, JA_ANC_COMP = 6, JA_
 // vs_f: floats of saved predicted velocities (learned warm start, restitution), 0 without
 // ghist: the reverse reads the sweeps' impulse history from the saved working
 // sets in global memory; otherwise (replays) the adjoint layout holds it
+// The row set-up's sphere centres (cen) are kept where the env has at least
+// two candidate pairs per body, each centre then taking part in four tests or
+// more.  With fewer they would save little and could make the layout of a
+// large env exceed the LDS (460 bodies, three of them with a sphere-sphere
+// sphere: 159 KB without, 164 KB with them); a test forms its two centres.
+SHD bool keeps_centres(int nb, int P) { return P >= 2 * nb; }
 SHD Lay make_lay(int nb, int nj, int G, int P, int ncol, int ncand, int nvis, int nslot, int lam, int n_iters,
                  bool adj,
                  int mlp_f = 0, int mlp_a = 0, int vs_f = 0, bool ghist = false) {
@@ -206,7 +212,7 @@ SHD Lay make_lay(int nb, int nj, int G, int P, int ncol, int ncand, int nvis, in
   L.gs = o; o += align4(G * 4);
   L.topo = o; o += align4(2 * nj + G + P + ncol + 1 + ncand);
   L.misc = o; o += MISC_N;
-  L.cen = o; o += P > 0 ? 4 * nb : 0;
+  L.cen = o; o += keeps_centres(nb, P) ? 4 * nb : 0;
   L.body = o; o += align4((nb + 1) * BS);   // bodies and the world slot (index nb)
   L.ctl = o; o += align4(nj);
   L.ws = o; o += align4(lam);
@@ -266,7 +272,8 @@ struct Env {
   // joint (the same each step), then the placed contacts in canonical order
   SHD i4* plan() const { return (i4*)(L + lay.plan); }
   SHD i4* vis() const { return (i4*)(L + lay.vis); }
-  // (row set-up) world centre and radius of each body's sphere-sphere sphere
+  // (row set-up, with keeps_centres) world centre and radius of each body's
+  // sphere-sphere sphere
   SHD float* cen(int b) const { return L + lay.cen + 4 * b; }
   SHD float* ctl() const { return L + lay.ctl; }   // the step's control of each joint
   SHD float* misc() const { return L + lay.misc; }
@@ -813,14 +820,21 @@ SHD void build_contact(const DevModel& M, const Env& E, int code, int s, const C
   E.row(s + 2)[RBI] = E.row(s + 2)[RBA] = 0.f;
 }
 
+// World centre and radius of a body's sphere-sphere sphere.
+SHD f4 pair_sphere(const Env& E, int b) {
+  const float* B = E.body(b);
+  const f3 c = ld3(B + BP) + mv(B + BR, ld3(B + BPO));
+  return f4{c.x, c.y, c.z, B[BPR]};
+}
+
 // F4: test the contact candidates, compact the active ones, build rows.
 // Inactive contact candidates have their stored impulses cleared.
 //
 // Candidates are tested in canonical order, a lane each and as many at a time
 // as the team has lanes (whatever their colour: a colour of a long chain holds
 // a dozen pairs, few of them near, and a pass per colour spent most of the
-// row set-up on its latency).  The sphere centres are formed once per body, and
-// a pair whose squared distance is clearly out of reach takes no root.  The
+// row set-up on its latency).  Where an env has pairs enough (keeps_centres)
+// the sphere centres are formed once per body, and a pair whose squared distance is clearly out of reach takes no root.  The
 // k-th active candidate takes the k-th row slot; beyond the env's capacity it
 // is dropped, its stored impulse cleared and the env flagged.  (Chains of 2..32
 // bodies, forward step: 45 of 103 thousand cycles per wave in a pass per
@@ -838,12 +852,9 @@ SHD void f_rows(const Team& tm, const DevModel& M, const Env& E, bool act) {
   // at once, lanes over joints.
   const int nj = act ? E.nj : 0;
   for (int j = tm.tl; j < nj; j += tm.ts) build_joint(M, E, j, E.jr * j);
-  if (E.P > 0)
-    for (int b = tm.tl; b < (act ? E.nb : 0); b += tm.ts) {
-      const float* B = E.body(b);
-      const f3 c = ld3(B + BP) + mv(B + BR, ld3(B + BPO));
-      st4(E.cen(b), f4{c.x, c.y, c.z, B[BPR]});
-    }
+  const bool centres = keeps_centres(E.nb, E.P);
+  if (centres)
+    for (int b = tm.tl; b < (act ? E.nb : 0); b += tm.ts) st4(E.cen(b), pair_sphere(E, b));
   tm.sync();
   int ncon = 0;   // active contacts so far, placed while below ccap (team-uniform)
   const int ncc = act ? E.ncand - E.nj : 0;
@@ -862,7 +873,9 @@ SHD void f_rows(const Team& tm, const DevModel& M, const Env& E, bool act) {
         const f3 c = ld3(B + BP) + mv(B + BR, ld3(S));
         on = c.z - S[3] < M.spec;
       } else {
-        const f4 ca = ld4(E.cen(rb.a)), cb = ld4(E.cen(rb.b));
+        f4 ca, cb;
+        if (centres) { ca = ld4(E.cen(rb.a)); cb = ld4(E.cen(rb.b)); }
+        else { ca = pair_sphere(E, rb.a); cb = pair_sphere(E, rb.b); }
         const f3 d = mk3(cb.x, cb.y, cb.z) - mk3(ca.x, ca.y, ca.z);
         const float reach = (ca.w + cb.w + M.spec) * 1.0001f;
         if (!(reach > 1e-3f) || !(dot(d, d) > reach * reach)) on = len3(d) - ca.w - cb.w < M.spec;
