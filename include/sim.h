@@ -153,7 +153,9 @@ typedef struct {
   int32_t loss_mask;             /* bit k: coordinate k enters the loss */
   int32_t ckpt_every;            /* K_ck: rollout stores the state every K_ck steps */
   int32_t min_team;              /* 0: automatic; else lanes per env are at least this
-                                    (power of two <= 64).  Results do not depend on it. */
+                                    (power of two <= 64), and the automatic choice's wider
+                                    teams for models of few envs are left out, so that 1 can
+                                    give narrower teams than 0.  Results do not depend on it. */
   int32_t ctrl_kind;             /* SIM_CTRL_* */
   int32_t mlp_sizes[4];          /* in, h1, h2, out; every env has out = J_e + mlp_rec,
                                     in = 2 J_e + 2 + mlp_rec; h1, h2 <= 256 */
@@ -491,7 +493,10 @@ sim_status sim_render_grad(sim_handle h, const float* x, const sim_camera* cam, 
  * the speed does.  sim_tune times, for each bucket, the forward rollout (and,
  * if with_grad, rollout_grad) of that bucket alone at each admissible width
  * (powers of two from the narrowest the bucket's envs allow whose tile fits
- * LDS; the first max_candidates of them), keeps the fastest, and writes the
+ * LDS: a lane for every joint of a colour, half a lane per body, min_team; for
+ * a bucket merged of several size classes, the width it was made with.  The
+ * width the model was made with is timed first, then from the narrowest on,
+ * max_candidates in all), keeps the fastest, and writes the
  * chosen widths to teams[] (host, up to cap entries, may be NULL).  x0 and u
  * are as for rollout.  Synchronous; allocates and frees its own temporaries
  * (checkpoints, workspace).  Returns the number of buckets or a negative

@@ -20,7 +20,7 @@ struct HostEnv {
   int nb = 0, nj = 0, G = 0, P = 0, ncol = 0, ncand = 0, ccap = 0, nslot = 0, lam = 0;
   std::vector<int> topo;   // jpar, jchi, gbody, pcode, colstart, cand
   std::vector<float> cst;
-  int team = 1;
+  int team = 1, team_min = 1;
   int fwd_floats = 0, adj_floats = 0, adj_floats_ring = 0;
   int dump_floats = 0;     // one step's saved working set (see drivers.h)
 };
@@ -112,10 +112,12 @@ sim_status build_env(const sim_model_desc& d, int e, bool keep_v, HostEnv& H) {
   H.P = (int)pcode.size();
   // colour-major candidate list
   std::vector<int> colstart, cand;
+  int max_col = 1;
   for (int c = 0; c < njc; ++c) {
     colstart.push_back((int)cand.size());
     for (int j = 0; j < H.nj; ++j)
       if (jcol[j] == c) cand.push_back((K_JOINT << 24) | j);
+    max_col = std::max(max_col, (int)cand.size() - colstart.back());
   }
   for (int k = 0; k < nsub; ++k) {
     colstart.push_back((int)cand.size());
@@ -194,8 +196,9 @@ sim_status build_env(const sim_model_desc& d, int e, bool keep_v, HostEnv& H) {
   H.cst[8 * H.nb + JS * H.nj + 4 * H.G] = d.mu[e];
   H.cst[8 * H.nb + JS * H.nj + 4 * H.G + 1] = d.restitution ? d.restitution[e] : 0.f;
   // team size: a pair of lanes for every joint (up to the wave), enough lanes
-  // for half the bodies
+  // for half the bodies; at the least a lane for each joint of the widest colour
   H.team = std::min(64, next_pow2(std::max({1, 2 * H.nj, (H.nb + 1) / 2})));
+  H.team_min = std::min(64, next_pow2(std::max({1, max_col, (H.nb + 1) / 2})));
   int mf = 0, ma = 0;
   if (d.ctrl_kind == 1) {
     const int rec = d.mlp_rec;
@@ -226,6 +229,7 @@ sim_status pack_model(const sim_model_desc* d, PackedModel& P, std::string& err)
   P.target.assign(3 * (size_t)E, 0.f);
   P.lam_off.assign(E + 1, 0);
   P.team_of.assign(E, 1);
+  P.team_min_of.assign(E, 1);
   P.fwd_of.assign(E, 0);
   P.adj_of.assign(E, 0);
   P.adj_ring_of.assign(E, 0);
@@ -262,6 +266,7 @@ sim_status pack_model(const sim_model_desc* d, PackedModel& P, std::string& err)
     for (int k = 0; k < 3; ++k) P.target[3 * e + k] = d->target[3 * e + k];
     P.lam_off[e + 1] = P.lam_off[e] + H.lam;
     P.team_of[e] = H.team;
+    P.team_min_of[e] = H.team_min;
     P.fwd_of[e] = H.fwd_floats;
     P.adj_of[e] = H.adj_floats;
     P.adj_ring_of[e] = H.adj_floats_ring;

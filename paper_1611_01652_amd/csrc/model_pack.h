@@ -10,6 +10,7 @@ namespace sim {
 
 struct PackedModel {
   std::vector<int> hdr, topo, lam_off, team_of, fwd_of, adj_of, ccap_of;
+  std::vector<int> team_min_of;   // narrowest team (team_of: the one that holds the joints' rows in registers)
   std::vector<int> adj_ring_of;   // adjoint LDS floats with the impulse history in global memory (saved working sets)
   std::vector<float> cst, target;
   long long seg_total = 0;   // floats of the reverse sweep's buffer (all envs)

@@ -58,6 +58,7 @@ sim_status fail(sim_status s, const std::string& msg) {
 struct Bucket {
   int team = 1;
   int team_min = 1;             // narrowest team the bucket's envs allow
+  int team_def = 1;             // the width it is made with
   std::vector<int> envs_host;   // tiles * (64/team)
   int n_tiles = 0;
   int floats_fwd = 0, floats_adj = 0;
@@ -380,11 +381,13 @@ std::vector<int> merge_classes(const DevModel& M, const std::vector<EnvClass>& c
 }
 
 // Team widths a bucket may use: powers of two from its narrowest whose tile
-// fits the device's LDS.
+// fits the device's LDS.  The width it is made with comes first (a tuner that
+// may time only a few never ends on a slower one), then from the narrowest.
 std::vector<int> admissible_teams(const sim_model* h, const Bucket& b) {
-  std::vector<int> out;
+  std::vector<int> out{b.team_def};
   for (int t = b.team_min; t <= 64; t *= 2)
-    if (std::max(adj_bytes(h->M, t, b.floats_adj), fwd_bytes(h->M, t, b.floats_fwd, b.ccap_max)) <= h->max_lds)
+    if (t != b.team_def &&
+        std::max(adj_bytes(h->M, t, b.floats_adj), fwd_bytes(h->M, t, b.floats_fwd, b.ccap_max)) <= h->max_lds)
       out.push_back(t);
   return out;
 }
@@ -611,8 +614,11 @@ sim_status sim_init(const sim_model_desc* d, sim_handle* out) {
       return adj_of[a] > adj_of[b];
     });
     Bucket bk;
-    bk.team = team;
-    bk.team_min = team;
+    bk.team = bk.team_def = team;
+    // One class: from its envs' narrowest.  Several merged: from the width the
+    // merge was chosen at (a narrower tile reserves the largest env's LDS once
+    // more for every env it takes on).
+    bk.team_min = c1 - c0 > 1 ? team : std::max(1, d->min_team);
     const int epw = 64 / team;
     bk.n_tiles = ((int)ids.size() + epw - 1) / epw;
     bk.envs_host.assign((size_t)bk.n_tiles * epw, -1);
@@ -621,6 +627,7 @@ sim_status sim_init(const sim_model_desc* d, sim_handle* out) {
       bk.floats_fwd = std::max(bk.floats_fwd, fwd_of[ids[i]]);
       bk.floats_adj = std::max(bk.floats_adj, adj_of[ids[i]]);
       bk.ccap_max = std::max(bk.ccap_max, P.ccap_of[ids[i]]);
+      if (c1 - c0 == 1) bk.team_min = std::max(bk.team_min, P.team_min_of[ids[i]]);
     }
     max_lds = std::max(max_lds, (int)std::max(adj_bytes(M, team, bk.floats_adj),
                                               fwd_bytes(M, team, bk.floats_fwd, bk.ccap_max)));

@@ -82,21 +82,22 @@ def tune_call(sim, x0, u, gain=0.05, reps=2, log=None):
     best = call_ms(sim, x0, u, reps)
     if log is not None:
         log(teams.tolist(), best)
-    for i in range(len(teams)):
-        t = int(teams[i]) * 2
-        while t <= 64:
-            trial = teams.copy()
-            trial[i] = t
-            try:
-                sim.set_teams(trial)
-            except SimError:
-                break
-            ms = call_ms(sim, x0, u, reps)
-            if log is not None:
-                log(trial.tolist(), ms)
-            if ms < best * (1.0 - gain):
-                best, teams = ms, trial
-            t *= 2
+    for i, default in enumerate(teams.tolist()):
+        wider = [default << k for k in range(1, 7) if default << k <= 64]
+        narrower = [default >> k for k in range(1, 7) if default >> k >= 1]
+        for widths in (wider, narrower):   # each until one is not admissible
+            for t in widths:
+                trial = teams.copy()
+                trial[i] = t
+                try:
+                    sim.set_teams(trial)
+                except SimError:
+                    break
+                ms = call_ms(sim, x0, u, reps)
+                if log is not None:
+                    log(trial.tolist(), ms)
+                if ms < best * (1.0 - gain):
+                    best, teams = ms, trial
         sim.set_teams(teams)
     return teams
 
