@@ -173,16 +173,24 @@ __device__ __forceinline__ void trace_spheres(const float4* cs, unsigned long lo
   }
 }
 
-// A wave's pixels: tiles of kTileW x kTileH, lane l at column l % kTileW, row
-// l / kTileW (64-byte runs of an image row).  Few of an env's spheres are in
-// sight of so small a tile, so a wave first tests the staged spheres against
-// the tile, one per lane, and traces only those left.
-constexpr int kTileW = 16, kTileH = 4;
-static_assert(kTileW * kTileH == 64, "a tile is a wave");
-__device__ __forceinline__ int tiles_x(const RenderCam& cam) { return (cam.width + kTileW - 1) / kTileW; }
-__device__ __forceinline__ int tiles_of(const RenderCam& cam) {
-  return tiles_x(cam) * ((cam.height + kTileH - 1) / kTileH);
-}
+// A wave's pixels: tiles of w() x h() = 64, lane l at column l % w(), row
+// l / w().  16 x 4 (64-byte runs of an image row), a constant of the kernel, but
+// for frames that fill those badly: the shape is then the frame's (tile_shape).
+// Few of an env's spheres are in sight of so small a tile, so a wave first
+// tests the staged spheres against the tile, one per lane, and traces only
+// those left.
+constexpr int kTileLg = 4;   // log2 of the usual tile's width
+template <int LG>            // log2 of the tile's width; -1: the launch's choice
+struct Tiles {
+  int chosen;
+  __host__ __device__ __forceinline__ int lg() const { return LG >= 0 ? LG : chosen; }
+  __host__ __device__ __forceinline__ int w() const { return 1 << lg(); }
+  __host__ __device__ __forceinline__ int h() const { return 64 >> lg(); }
+  __host__ __device__ __forceinline__ int across(const RenderCam& cam) const { return (cam.width + w() - 1) >> lg(); }
+  __host__ __device__ __forceinline__ int count(const RenderCam& cam) const {
+    return across(cam) * ((cam.height + h() - 1) >> (6 - lg()));
+  }
+};
 // Every ray of the tile has |d - dc| <= rho for the tile's centre ray dc and
 // rho = half the pixel span along u and v (the triangle inequality: nothing
 // is asked of the axes), so a hit at some s >= 1 needs |s dc - m| <= r + s rho
@@ -190,9 +198,10 @@ __device__ __forceinline__ int tiles_of(const RenderCam& cam) {
 // dc . m + r rho, g = |m|^2 - r^2.  A sphere is left out when f has no root,
 // or none that is positive, by margins (1e-5 of the terms) far above the FP32
 // rounding here and in trace_spheres; anything not finite is kept.
-__device__ __forceinline__ bool sphere_in_tile(const float4 cc, const RenderCam& cam, int i0, int j0) {
-  const float u = ((float)(i0 + kTileW / 2) - 0.5f * (float)cam.width) * cam.pitch;
-  const float v = (0.5f * (float)cam.height - (float)(j0 + kTileH / 2)) * cam.pitch;
+template <int LG>
+__device__ __forceinline__ bool sphere_in_tile(const float4 cc, const RenderCam& cam, Tiles<LG> tiles, int i0, int j0) {
+  const float u = (((float)i0 + 0.5f * (float)tiles.w()) - 0.5f * (float)cam.width) * cam.pitch;
+  const float v = (0.5f * (float)cam.height - ((float)j0 + 0.5f * (float)tiles.h())) * cam.pitch;
   float ex = 0.f, ey = 0.f, a = 0.f, b = 0.f, m2 = 0.f;
   const float c[3] = {cc.x, cc.y, cc.z};
   for (int k = 0; k < 3; ++k) {
@@ -203,24 +212,26 @@ __device__ __forceinline__ bool sphere_in_tile(const float4 cc, const RenderCam&
     b += d * m;
     m2 += m * m;
   }
-  const float rho = 1.001f * cam.pitch * (0.5f * kTileW * sqrtf(ex) + 0.5f * kTileH * sqrtf(ey));
+  const float rho = 0.5005f * cam.pitch * ((float)tiles.w() * sqrtf(ex) + (float)tiles.h() * sqrtf(ey));
   const float A = a - rho * rho, q = b + cc.w * rho, g = m2 - cc.w * cc.w;
   const float disc = q * q - A * g;
   return !(A > 1e-3f * a && (disc < -1e-5f * (q * q + fabsf(A * g)) || (q < 0.f && g > 1e-5f * m2)));
 }
 // The staged spheres to trace in one tile, a lane each ...
-__device__ __forceinline__ unsigned long long tile_spheres(const float4* cs, int n, const RenderCam& cam, int i0,
-                                                           int j0, int lane) {
-  return __ballot(lane < n && sphere_in_tile(cs[lane], cam, i0, j0));
+template <int LG>
+__device__ __forceinline__ unsigned long long tile_spheres(const float4* cs, int n, const RenderCam& cam,
+                                                           Tiles<LG> tiles, int i0, int j0, int lane) {
+  return __ballot(lane < n && sphere_in_tile(cs[lane], cam, tiles, i0, j0));
 }
 // ... or, of at most 16 spheres, in the four tiles tile, tile + step, ..: 16
 // bits each.  (A test is 60 instructions, most of what a tile without spheres
 // costs the gradient: 65 -> 51 us for 512 images.  The image, where every
 // tile has the ground, got slower with it: 98 -> 111 us.)
-__device__ __forceinline__ unsigned long long tile_spheres_x4(const float4* cs, int n, const RenderCam& cam, int tile,
-                                                              int step, int tx, int lane) {
+template <int LG>
+__device__ __forceinline__ unsigned long long tile_spheres_x4(const float4* cs, int n, const RenderCam& cam,
+                                                              Tiles<LG> tiles, int tile, int step, int tx, int lane) {
   const int k = lane & 15, t = tile + (lane >> 4) * step;
-  return __ballot(k < n && sphere_in_tile(cs[k], cam, t % tx * kTileW, t / tx * kTileH));
+  return __ballot(k < n && sphere_in_tile(cs[k], cam, tiles, t % tx * tiles.w(), t / tx * tiles.h()));
 }
 
 __device__ __forceinline__ void trace_ground(const RenderScene& sc, const Ray& ray, RHit& h) {
@@ -268,17 +279,18 @@ constexpr int kTilesPerWave = 8;
 // (the ground's FP64 intersection the largest part) and the texel loads.  512
 // images of 288 x 96 over chains of 2..16 spheres: 98 us, 57 MB written; with
 // every sphere tested per pixel, fmod and four texel loads 153 us.
-__global__ __launch_bounds__(256) void k_render(RenderScene sc, const float* x, RenderCam cam, RenderTex tex,
-                                                float* image) {
+template <int LG>
+__global__ __launch_bounds__(256) void k_render(RenderScene sc, const float* x, RenderCam cam, Tiles<LG> tiles,
+                                                RenderTex tex, float* image) {
   __shared__ float4 cs[kStage];
   const int e = blockIdx.y, lane = threadIdx.x & 63;
-  const int n = cam.width * cam.height, tx = tiles_x(cam), nt = tiles_of(cam);
+  const int n = cam.width * cam.height, tx = tiles.across(cam), nt = tiles.count(cam);
   const int s0 = sc.env_sph[e], s1 = sc.env_sph[e + 1];
   const RenderInv inv{1.0 / (double)tex.cell, 1.0 / (double)tex.gnx, 1.0 / (double)tex.gny};
   for (int q = 0; q < kTilesPerWave; ++q) {
     const int tile = (blockIdx.x * kTilesPerWave + q) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int i0 = tile % tx * kTileW, j0 = tile / tx * kTileH;
-    const int i = i0 + lane % kTileW, j = j0 + lane / kTileW;
+    const int i0 = tile % tx * tiles.w(), j0 = tile / tx * tiles.h();
+    const int i = i0 + (lane & (tiles.w() - 1)), j = j0 + (lane >> tiles.lg());
     const Ray ray = pixel_ray(cam, i, j);
     RHit h{-2, INFINITY};
     for (int g0 = s0; g0 < s1; g0 += kStage) {
@@ -288,7 +300,7 @@ __global__ __launch_bounds__(256) void k_render(RenderScene sc, const float* x, 
         stage_spheres(sc, x, g0, g1, cs);
         __syncthreads();
       }
-      const unsigned long long mask = tile_spheres(cs, g1 - g0, cam, i0, j0, lane);
+      const unsigned long long mask = tile_spheres(cs, g1 - g0, cam, tiles, i0, j0, lane);
       if (mask) trace_spheres(cs, mask, g0 - s0, ray, ray_ia(ray), h);
     }
     if (tile < nt && i < cam.width && j < cam.height)
@@ -327,14 +339,16 @@ constexpr int kGradThreads = 64 * kGradWaves;
 // added in wave order and each sphere's sums go to its body, spheres in env
 // order.  Every sum runs in an order fixed by the inputs, so the gradient is
 // bitwise reproducible.
+template <int LG>
 __global__ __launch_bounds__(kGradThreads) void k_render_grad(RenderScene sc, const float* x, RenderCam cam,
-                                                              RenderTex tex, const float* w, float* g_x) {
+                                                              Tiles<LG> tiles, RenderTex tex, const float* w,
+                                                              float* g_x) {
   __shared__ float4 cs[kRenderMaxSpheres];
   __shared__ float rot[kRenderMaxSpheres][12];   // body rotation 9, sphere offset 3
   __shared__ float acc[kGradWaves][kRenderMaxSpheres][12];
   __shared__ float tot[kRenderMaxSpheres][12];
   const int e = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int n = cam.width * cam.height, tx = tiles_x(cam), nt = tiles_of(cam);
+  const int n = cam.width * cam.height, tx = tiles.across(cam), nt = tiles.count(cam);
   const int s0 = sc.env_sph[e], ns = sc.env_sph[e + 1] - s0;
   for (int u = t; u < kGradWaves * kRenderMaxSpheres * 12; u += kGradThreads) (&acc[0][0][0])[u] = 0.f;
   stage_spheres(sc, x, s0, s0 + ns, cs);
@@ -347,11 +361,11 @@ __global__ __launch_bounds__(kGradThreads) void k_render_grad(RenderScene sc, co
   const float kx = 0.5f * (float)(tex.snx - 1), ky = 0.5f * (float)(tex.sny - 1);
   unsigned long long four = 0;
   for (int tile = wv, q = 0; tile < nt; tile += kGradWaves, ++q) {
-    if (q % 4 == 0) four = tile_spheres_x4(cs, ns, cam, tile, kGradWaves, tx, lane);
+    if (q % 4 == 0) four = tile_spheres_x4(cs, ns, cam, tiles, tile, kGradWaves, tx, lane);
     const unsigned long long mask = four >> (16 * (q % 4)) & 0xffffull;
     if (mask == 0) continue;
-    const int i0 = tile % tx * kTileW, j0 = tile / tx * kTileH;
-    const int i = i0 + lane % kTileW, j = j0 + lane / kTileW;
+    const int i0 = tile % tx * tiles.w(), j0 = tile / tx * tiles.h();
+    const int i = i0 + (lane & (tiles.w() - 1)), j = j0 + (lane >> tiles.lg());
     int hk = -1;
     float v[12];
     for (int c = 0; c < 12; ++c) v[c] = 0.f;
@@ -429,22 +443,56 @@ __global__ __launch_bounds__(kGradThreads) void k_render_grad(RenderScene sc, co
   }
 }
 
+// log2 of the width of the frame's tiles: 16, unless another width needs less
+// than two thirds of the tiles, then the one that needs the fewest, the nearest
+// to 16 of equal ones.  Frames one or a few pixels wide or high leave most
+// lanes of a 16 x 4 tile idle (512 images and their gradient, 16 x 4 -> chosen:
+// 1 x 2048 pixels 110 -> 44 us, 2048 x 1 73 -> 49 us).  As a constant of the
+// kernels the 16 x 4 shape is 1 to 2 % faster than as an argument, so the usual
+// frames have kernels of their own.
+int tile_shape(const RenderCam& cam) {
+  const long long whole = Tiles<kTileLg>{}.count(cam);
+  long long least = whole;
+  int lg = kTileLg;
+  for (int k : {3, 5, 2, 6, 1, 0}) {
+    const long long n = Tiles<-1>{k}.count(cam);
+    if (3 * n < 2 * whole && n < least) {
+      least = n;
+      lg = k;
+    }
+  }
+  return lg;
+}
+
+template <int LG>
+void render_frame(const RenderScene& sc, const float* x, const RenderCam& cam, Tiles<LG> tiles, const RenderTex& tex,
+                  float* image, hipStream_t st) {
+  const dim3 grid((tiles.count(cam) + 4 * kTilesPerWave - 1) / (4 * kTilesPerWave), sc.E);
+  hipLaunchKernelGGL(k_render<LG>, grid, dim3(256), 0, st, sc, x, cam, tiles, tex, image);
+}
+
 }  // namespace
 
 hipError_t launch_render(const RenderScene& sc, const float* x, const RenderCam& cam, const RenderTex& tex,
                          float* image, hipStream_t st) {
   const int n = cam.width * cam.height;
   if (sc.E == 0 || n == 0) return hipSuccess;
-  const int tiles = ((cam.width + kTileW - 1) / kTileW) * ((cam.height + kTileH - 1) / kTileH);
-  const dim3 grid((tiles + 4 * kTilesPerWave - 1) / (4 * kTilesPerWave), sc.E);
-  hipLaunchKernelGGL(k_render, grid, dim3(256), 0, st, sc, x, cam, tex, image);
+  const int lg = tile_shape(cam);
+  if (lg == kTileLg) render_frame(sc, x, cam, Tiles<kTileLg>{lg}, tex, image, st);
+  else render_frame(sc, x, cam, Tiles<-1>{lg}, tex, image, st);
   return hipGetLastError();
 }
 
 hipError_t launch_render_grad(const RenderScene& sc, const float* x, const RenderCam& cam, const RenderTex& tex,
                               const float* w, float* g_x, hipStream_t st) {
   if (sc.E == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_render_grad, dim3(sc.E), dim3(kGradThreads), 0, st, sc, x, cam, tex, w, g_x);
+  const int lg = tile_shape(cam);
+  if (lg == kTileLg)
+    hipLaunchKernelGGL(k_render_grad<kTileLg>, dim3(sc.E), dim3(kGradThreads), 0, st, sc, x, cam, Tiles<kTileLg>{lg},
+                       tex, w, g_x);
+  else
+    hipLaunchKernelGGL(k_render_grad<-1>, dim3(sc.E), dim3(kGradThreads), 0, st, sc, x, cam, Tiles<-1>{lg}, tex, w,
+                       g_x);
   return hipGetLastError();
 }
 
