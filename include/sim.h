@@ -414,7 +414,8 @@ sim_status sim_env_buckets(sim_handle h, int32_t* bucket_of_env);
 /* ---- Replayable step sequences (HIP graphs). ----
  * Captures n_steps consecutive sim_step calls into a HIP graph, for callers
  * that step the simulation in a loop (a policy in the loop, serving): one
- * sim_graph_launch then costs one graph launch and one kernel per bucket, with
+ * sim_graph_launch then costs one graph launch and one kernel per bucket (and
+ * one that clears its tile queue, for models that fill the device), with
  * every env's state kept on chip between its steps.  Nothing runs at capture time.
  *   x: device [2][18][B]; step k reads x[k % 2] and writes x[(k + 1) % 2],
  *      so the result is in x[n_steps % 2].
@@ -427,7 +428,7 @@ sim_status sim_env_buckets(sim_handle h, int32_t* bucket_of_env);
  *      non-finite state stays non-finite, so it is still flagged).
  * The pointers are baked into the graph: every launch reads and writes the
  * same buffers.  A graph must not run concurrently with another call on the
- * same handle (they share its streams and events).  Release with sim_graph_destroy;
+ * same handle (they share its streams, events and tile queues).  Release with sim_graph_destroy;
  * while graphs of a handle are alive, sim_destroy, sim_tune and
  * sim_set_teams refuse with SIM_E_STATE (the graphs use its tile lists). */
 typedef struct sim_graph_s* sim_graph;

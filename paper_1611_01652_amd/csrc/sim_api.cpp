@@ -194,12 +194,21 @@ int grid_for(const sim_model* h, long long units, long long bytes) {
 }
 int grid_for(const sim_model* h, const Bucket& b, long long bytes) { return grid_for(h, b.n_tiles, bytes); }
 
-// One bucket's kernels (queue reset, but for steps, + launch) on stream sx.
+// One bucket's kernels (queue reset + launch) on stream sx.  Steps take their
+// tiles from the queue where workgroups take several tiles and these are long
+// or uneven: several steps, or sweeps to a tolerance (16384 chains of 2..16
+// bodies, 8 tolerance steps: 17.9 ms, tiles dealt out in turn 19.6; 8192
+// quadrupeds, 8 steps: 2.96 and 3.65).  Otherwise they are dealt out in turn,
+// which saves the reset, a launch per bucket (64 arms 37 -> 23 us a step; one
+// step of 65536 arms 248 us, with the queue 257; 16384 chains 515 and 530).
 bool bucket_step(sim_model* h, size_t i, const DevModel& M, const StepArgs& a, hipStream_t sx) {
   const Bucket& b = h->buckets[i];
-  TileSet ts{b.envs_dev, b.n_tiles, b.floats_fwd, nullptr, 1};
   const long long lds = fwd_bytes(h, b);
-  return launch_step(M, ts, b.team, grid_for(h, b, lds), (size_t)lds, a, sx) == hipSuccess;
+  const int grid = grid_for(h, b, lds);
+  const bool queued = b.n_tiles > grid && (a.n_steps > 1 || M.solve_mode == SIM_SOLVE_TOL);
+  TileSet ts{b.envs_dev, b.n_tiles, b.floats_fwd, queued ? h->d_queue + i : nullptr, 1};
+  if (queued && launch_zero(ts.queue, 1, sx) != hipSuccess) return false;
+  return launch_step(M, ts, b.team, grid, (size_t)lds, a, sx) == hipSuccess;
 }
 bool bucket_rollout(sim_model* h, size_t i, const DevModel& M, const RolloutArgs& a, hipStream_t sx) {
   const Bucket& b = h->buckets[i];

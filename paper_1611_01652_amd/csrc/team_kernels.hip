@@ -263,9 +263,10 @@ __global__ __launch_bounds__(64) void k_step(DevModel M, TileSet ts, StepArgs a)
   setup_shared(tm, M, lds, ts.env_floats, SOLVE != 0);
   const int team = threadIdx.x / TEAM;
   constexpr int EPW = 64 / TEAM;
-  // (the steps of a bucket's tiles cost alike, so the tiles are dealt out in
-  // turn: no queue to reset, which was a launch of its own per bucket)
-  for (int tile = blockIdx.x; tile < ts.n_tiles; tile += gridDim.x) {
+  // (without a queue the tiles are dealt out in turn, see bucket_step)
+  const bool q = ts.queue != nullptr;
+  for (int tile = q ? next_tile(ts.queue) : (int)blockIdx.x; tile < ts.n_tiles;
+       tile = q ? next_tile(ts.queue) : tile + (int)gridDim.x) {
     const int ie = ts.envs[tile * EPW + team];
     const bool valid = ie >= 0;
     Env E = make_env(M, valid ? ie : ts.envs[tile * EPW], lds + team * ts.env_floats, M.n_iters, false);
