@@ -210,12 +210,29 @@ bool bucket_step(sim_model* h, size_t i, const DevModel& M, const StepArgs& a, h
   if (queued && launch_zero(ts.queue, 1, sx) != hipSuccess) return false;
   return launch_step(M, ts, b.team, grid, (size_t)lds, a, sx) == hipSuccess;
 }
+// Waves per SIMD for fixed-sweep rollouts: two where the model's tiles (the
+// buckets run at once) are more than the device has SIMDs and some bucket's
+// tiles are small enough that a CU's LDS holds more than one per SIMD.
+// Where each wave has a SIMD to itself the kernel with more registers is up to
+// 3 % faster.  One wave per SIMD -> two: 100000 balls 1134 -> 890 us, 8192
+// quadrupeds 4.43 -> 3.18 ms, 16384 chains of 2..32 bodies 6.01 -> 5.45 ms;
+// 4096 arms, two waves per CU, 1761 -> 1818 us (and so not taken there).
+int waves_per_simd(const sim_model* h) {
+  long long tiles = 0;
+  bool small = false;
+  for (const Bucket& b : h->buckets) {
+    tiles += b.n_tiles;
+    small = small || fwd_bytes(h, b) * (kSimdsPerCu + 1) <= kLdsPerCu;
+  }
+  return small && tiles > kSimdsPerCu * (long long)h->n_cu ? 2 : 1;
+}
 bool bucket_rollout(sim_model* h, size_t i, const DevModel& M, const RolloutArgs& a, hipStream_t sx) {
   const Bucket& b = h->buckets[i];
   TileSet ts{b.envs_dev, b.n_tiles, b.floats_fwd, h->d_queue + i, 1};
   if (launch_zero(ts.queue, 1, sx) != hipSuccess) return false;
   const long long lds = fwd_bytes(h, b);
   if (a.seg) return launch_rollout_keep(M, ts, b.team, grid_for(h, b, lds), (size_t)lds, a, sx) == hipSuccess;
+  ts.waves = waves_per_simd(h);
   return launch_rollout(M, ts, b.team, grid_for(h, b, lds), (size_t)lds, a, sx) == hipSuccess;
 }
 // Trajectory mode: the recompute of every segment of one bucket's envs into
