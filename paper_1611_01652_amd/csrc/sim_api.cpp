@@ -284,52 +284,55 @@ sim_status launch_steps(sim_model* h, const float* x_in, float* x_out, const flo
                      "sim_step launch");
 }
 
-// Hardware queues HIP spreads a process's streams over.
+// Hardware queues HIP spreads a process's streams over (at most kMaxQueues are
+// counted on, whatever the environment says).
+constexpr int kMaxQueues = 32;
 int hw_queues() {
   const char* v = std::getenv("GPU_MAX_HW_QUEUES");
   const int n = v ? std::atoi(v) : 0;
-  return n > 0 ? n : 4;
+  return n > 0 ? std::min(n, kMaxQueues) : 4;
 }
 
 // The buckets' streams, min(n, queues) of them on hardware queues of their own
-// (more buckets take the streams in turn, as their queues would).  HIP gives a new stream a queue by how many streams each has, and
-// a process that has made (and dropped) other streams can leave four new ones
-// on fewer than four queues, so that two of four buckets run in turn (333
-// chains by segments: 18.1 instead of 9.2 ms per call).  Which queue a stream
-// has cannot be asked, so it is tried: kernels on the streams chosen so far
-// wait, within a bound, for one on the new stream; if some of them does not see
-// it, the two share a queue (or the device is busy) and another stream is
-// tried, up to 2 x queues in all: 0.1 to 0.2 ms each, when a model of several
-// buckets is made.
+// (more buckets take the streams in turn, as their queues would).  HIP gives a
+// new stream a queue by how many streams each has, and a process that has made
+// (and dropped) other streams can leave four new ones on fewer than four
+// queues, so that two of four buckets run in turn (333 chains by segments:
+// 18.1 instead of 9.2 ms per call).  Which queue a stream has cannot be asked,
+// so it is tried: kernels on the streams chosen so far wait for one on the new
+// stream, for at most 100 us and 25 us for each of them; if some of them does
+// not see it, the two share a queue (or the device is busy) and another stream
+// is tried.  After max(8, twice the streams wanted) tries any streams are
+// taken: the waits sum to 1.4 ms at most for four streams, 14 ms for 15.
 bool make_streams(sim_model* h, int n, int queues) {
   auto create = [](hipStream_t* s) { return hipStreamCreateWithFlags(s, hipStreamNonBlocking) == hipSuccess; };
   const int want = std::min(n, queues);
   std::vector<hipStream_t> spare;
-  std::vector<int> seen(queues + 1, 0);
-  int* flags = nullptr;   // [0] the flag, [1 + i] what stream i's kernel saw
-  bool ok = hipMalloc((void**)&flags, seen.size() * sizeof(int)) == hipSuccess;
+  std::vector<int> seen(want, 0);
+  int* flag = h->d_queue;         // the try whose new stream has started
+  int* seen_dev = h->d_queue + 1; // what stream i's kernel saw of it
   // (the kernels' first launches, which load them, are not part of a try)
   hipStream_t first = nullptr;
-  ok = ok && create(&first);
+  bool ok = create(&first);
   if (ok) {
     h->streams.push_back(first);
-    ok = launch_set_flag(flags, first) == hipSuccess && launch_wait_flag(flags, flags + 1, 0, first) == hipSuccess &&
-         hipStreamSynchronize(first) == hipSuccess;
+    ok = launch_set_flag(flag, 1, first) == hipSuccess &&
+         launch_wait_flag(flag, 1, seen_dev, 0, first) == hipSuccess && hipStreamSynchronize(first) == hipSuccess;
   }
-  for (int tries = 1; ok && (int)h->streams.size() < want && tries < 2 * queues + 1; ++tries) {
+  const int last = 1 + std::max(8, 2 * want);
+  for (int t = 2; ok && (int)h->streams.size() < want && t <= last; ++t) {
     hipStream_t s;
     if (!(ok = create(&s))) break;
     const int k = (int)h->streams.size();
-    const long long ticks = 10000 + 2500 * k;   // of the 100 MHz clock: 100 us and 25 us a launch
-    ok = launch_zero(flags, k + 1, s) == hipSuccess && hipStreamSynchronize(s) == hipSuccess;
+    const long long ticks = 10000 + 2500 * k;   // of the 100 MHz clock
     for (int i = 0; ok && i < k; ++i)
-      ok = launch_wait_flag(flags, flags + 1 + i, ticks, h->streams[i]) == hipSuccess;
-    ok = ok && launch_set_flag(flags, s) == hipSuccess;
+      ok = launch_wait_flag(flag, t, seen_dev + i, ticks, h->streams[i]) == hipSuccess;
+    ok = ok && launch_set_flag(flag, t, s) == hipSuccess;
     for (int i = 0; i < k; ++i) ok = hipStreamSynchronize(h->streams[i]) == hipSuccess && ok;
     ok = hipStreamSynchronize(s) == hipSuccess && ok;
-    ok = ok && hipMemcpy(seen.data(), flags, (k + 1) * sizeof(int), hipMemcpyDeviceToHost) == hipSuccess;
+    ok = ok && hipMemcpy(seen.data(), seen_dev, k * sizeof(int), hipMemcpyDeviceToHost) == hipSuccess;
     bool alone = ok;
-    for (int i = 0; i < k; ++i) alone = alone && seen[1 + i] != 0;
+    for (int i = 0; i < k; ++i) alone = alone && seen[i] == t;
     (alone ? h->streams : spare).push_back(s);
   }
   // (fewer queues found than asked for: any of the streams)
@@ -338,7 +341,6 @@ bool make_streams(sim_model* h, int n, int queues) {
     spare.pop_back();
   }
   for (hipStream_t s : spare) (void)hipStreamDestroy(s);
-  if (flags) (void)hipFree(flags);
   return ok;
 }
 
@@ -659,6 +661,9 @@ sim_status sim_init(const sim_model_desc* d, sim_handle* out) {
                                               fwd_bytes(M, team, bk.floats_fwd, bk.ccap_max)));
     h->buckets.push_back(bk);
   }
+  // the tile queues' counters (and, first, the words the streams are tried with)
+  sim_status st = upload(&h->d_queue, std::vector<int>(h->buckets.size() + 1, 0));
+  if (st != SIM_OK) { release(h); return st; }
   // buckets run concurrently: on streams of default priority, forked from
   // and joined back to the caller's stream with events
   if (h->buckets.size() > 1) {
@@ -677,7 +682,6 @@ sim_status sim_init(const sim_model_desc* d, sim_handle* out) {
       return fail(SIM_E_DEVICE, "cannot create fork event");
     }
   }
-  sim_status st = SIM_OK;
   {
     // the camera's scene
     const int S = d->env_sphere_off[E];
@@ -702,10 +706,6 @@ sim_status sim_init(const sim_model_desc* d, sim_handle* out) {
   }
   for (auto& b : h->buckets)
     if ((st = upload(&b.envs_dev, b.envs_host)) != SIM_OK) { release(h); return st; }
-  if ((st = upload(&h->d_queue, std::vector<int>(std::max<size_t>(1, h->buckets.size()), 0))) != SIM_OK) {
-    release(h);
-    return st;
-  }
   // controller: clock table, weight-gradient tiles and parameter map
   if (d->ctrl_kind == 1) {
     const int in = d->mlp_sizes[0], n1 = d->mlp_sizes[1], n2 = d->mlp_sizes[2], no = d->mlp_sizes[3];

@@ -42,8 +42,8 @@ struct TeamLaunch {
   static hipError_t allow_lds(int bytes);   // dynamic LDS limit of this width's kernels
 };
 
-hipError_t launch_wait_flag(const int* flag, int* seen, long long ticks, hipStream_t st);
-hipError_t launch_set_flag(int* flag, hipStream_t st);
+hipError_t launch_wait_flag(const int* flag, int value, int* seen, long long ticks, hipStream_t st);
+hipError_t launch_set_flag(int* flag, int value, hipStream_t st);
 hipError_t launch_zero(int* p, int n, hipStream_t st);
 hipError_t launch_ctrl_transpose(const float* W, float* Wt, int in, int n1, int n2, int no, hipStream_t st);
 hipError_t launch_wgrad(const float* tape, int stride, int n_rows, int chunk, const WgradTile* tiles, int n_tiles,

@@ -100,24 +100,26 @@ __global__ void k_zero_ints(int* p, int n) {
 }
 
 // A lane that waits, for at most `ticks` of the 100 MHz clock, until *flag is
-// set, and writes whether it was; and the lane that sets it.  Two streams whose
+// `value`, and writes what it last saw; and the lane that sets it.  Two streams whose
 // kernels do not meet so share a hardware queue.
-__global__ void k_wait_flag(const int* flag, int* seen, long long ticks) {
+__global__ void k_wait_flag(const int* flag, int value, int* seen, long long ticks) {
   const long long t0 = wall_clock64();
   int v = 0;
-  while (v == 0 && wall_clock64() - t0 < ticks)
+  while (v != value && wall_clock64() - t0 < ticks)
     v = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   *seen = v;
 }
-__global__ void k_set_flag(int* flag) { __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__global__ void k_set_flag(int* flag, int value) {
+  __hip_atomic_store(flag, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // ------------------------------------------------------------------ launchers
-hipError_t launch_wait_flag(const int* flag, int* seen, long long ticks, hipStream_t st) {
-  hipLaunchKernelGGL(k_wait_flag, dim3(1), dim3(1), 0, st, flag, seen, ticks);
+hipError_t launch_wait_flag(const int* flag, int value, int* seen, long long ticks, hipStream_t st) {
+  hipLaunchKernelGGL(k_wait_flag, dim3(1), dim3(1), 0, st, flag, value, seen, ticks);
   return hipGetLastError();
 }
-hipError_t launch_set_flag(int* flag, hipStream_t st) {
-  hipLaunchKernelGGL(k_set_flag, dim3(1), dim3(1), 0, st, flag);
+hipError_t launch_set_flag(int* flag, int value, hipStream_t st) {
+  hipLaunchKernelGGL(k_set_flag, dim3(1), dim3(1), 0, st, flag, value);
   return hipGetLastError();
 }
 #define SIM_TEAMS(CALL)                                                                                      \
