@@ -11,7 +11,9 @@ namespace sim {
 struct PackedModel {
   std::vector<int> hdr, topo, lam_off, team_of, fwd_of, adj_of, ccap_of;
   std::vector<int> team_min_of;   // narrowest team (team_of: the one that holds the joints' rows in registers)
-  std::vector<int> adj_ring_of;   // adjoint LDS floats with the impulse history in global memory (saved working sets)
+  // adjoint LDS floats with the impulse history in global memory: what the
+  // reverse of saved working sets takes (then adj_of too; no ring is left)
+  std::vector<int> adj_ring_of;
   std::vector<float> cst, target;
   long long seg_total = 0;   // floats of the reverse sweep's buffer (all envs)
   long long tape_rows = 0;   // env-steps of the controller tape (sum of T_e)

@@ -94,6 +94,7 @@ SHD void kahan_add(float* sum, float* c, float x) {
 }
 
 // ------------------------------------------------------------------ model in global memory
+// (H_RING is read by nothing here; the host test harness writes it)
 enum { H_B0, H_NB, H_J0, H_NJ, H_LAMOFF, H_LAMSZ, H_G, H_P, H_NCOL, H_TOPO, H_CST, H_T, H_LB, H_CCAP,
        H_NCAND, H_ENV, H_SEG, H_NSLOT, H_TAPE, H_RING, H_COUNT };
 // candidate code: kind in the top byte
