@@ -194,6 +194,24 @@ int grid_for(const sim_model* h, long long units, long long bytes) {
 }
 int grid_for(const sim_model* h, const Bucket& b, long long bytes) { return grid_for(h, b.n_tiles, bytes); }
 
+// Waves per SIMD for fixed-sweep rollouts and steps: two where the model's
+// tiles (the buckets run at once) are more than the device has SIMDs and some
+// bucket's tiles are small enough that a CU's LDS holds more than one per
+// SIMD.  Where each wave has a SIMD to itself the kernel with more registers is
+// up to 3 % faster.  One wave per SIMD -> two: 100000 balls 1134 -> 890 us, 8192
+// quadrupeds 4.43 -> 3.18 ms, 16384 chains of 2..32 bodies 6.01 -> 5.45 ms;
+// 16 steps of 65536 arms 2.33 -> 1.50 ms; but 4096 arms, two waves per CU, 1761
+// -> 1818 us and a graph of 256 chains 357 -> 368 us, where it is not taken.
+int waves_per_simd(const sim_model* h) {
+  long long tiles = 0;
+  bool small = false;
+  for (const Bucket& b : h->buckets) {
+    tiles += b.n_tiles;
+    small = small || fwd_bytes(h, b) * (kSimdsPerCu + 1) <= kLdsPerCu;
+  }
+  return small && tiles > kSimdsPerCu * (long long)h->n_cu ? 2 : 1;
+}
+
 // One bucket's kernels (queue reset + launch) on stream sx.  Steps take their
 // tiles from the queue where workgroups take several tiles and these are long
 // or uneven: several steps, or sweeps to a tolerance (16384 chains of 2..16
@@ -207,24 +225,9 @@ bool bucket_step(sim_model* h, size_t i, const DevModel& M, const StepArgs& a, h
   const int grid = grid_for(h, b, lds);
   const bool queued = b.n_tiles > grid && (a.n_steps > 1 || M.solve_mode == SIM_SOLVE_TOL);
   TileSet ts{b.envs_dev, b.n_tiles, b.floats_fwd, queued ? h->d_queue + i : nullptr, 1};
+  ts.waves = waves_per_simd(h);
   if (queued && launch_zero(ts.queue, 1, sx) != hipSuccess) return false;
   return launch_step(M, ts, b.team, grid, (size_t)lds, a, sx) == hipSuccess;
-}
-// Waves per SIMD for fixed-sweep rollouts: two where the model's tiles (the
-// buckets run at once) are more than the device has SIMDs and some bucket's
-// tiles are small enough that a CU's LDS holds more than one per SIMD.
-// Where each wave has a SIMD to itself the kernel with more registers is up to
-// 3 % faster.  One wave per SIMD -> two: 100000 balls 1134 -> 890 us, 8192
-// quadrupeds 4.43 -> 3.18 ms, 16384 chains of 2..32 bodies 6.01 -> 5.45 ms;
-// 4096 arms, two waves per CU, 1761 -> 1818 us (and so not taken there).
-int waves_per_simd(const sim_model* h) {
-  long long tiles = 0;
-  bool small = false;
-  for (const Bucket& b : h->buckets) {
-    tiles += b.n_tiles;
-    small = small || fwd_bytes(h, b) * (kSimdsPerCu + 1) <= kLdsPerCu;
-  }
-  return small && tiles > kSimdsPerCu * (long long)h->n_cu ? 2 : 1;
 }
 bool bucket_rollout(sim_model* h, size_t i, const DevModel& M, const RolloutArgs& a, hipStream_t sx) {
   const Bucket& b = h->buckets[i];

@@ -13,7 +13,7 @@ struct TileSet {
   int env_floats;    // LDS floats reserved per env
   int* queue;        // device counter of the persistent tile queue
   int n_seg;         // trajectory recompute: segments per tile (units = n_tiles * n_seg)
-  int waves = 1;     // fixed-sweep rollouts: the waves per SIMD their kernel leaves room for
+  int waves = 1;     // fixed-sweep rollouts and steps: the waves per SIMD their kernel leaves room for
 };
 
 // One 32x32 output tile of the controller's weight-gradient contraction:

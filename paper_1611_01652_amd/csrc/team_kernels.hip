@@ -220,11 +220,11 @@ __device__ __forceinline__ int next_tile(int* queue) {
   return __shfl(v, 0);
 }
 
-// WAVES = 2 keeps the kernel within 256 registers, so that two waves share a
-// SIMD (the host takes it for models that have them, see waves_per_simd).
-// Unbounded it takes 276 to 286; the 10 to 20 values over are per-env ones
-// that are kept in scratch memory (40 to 76 bytes per lane) and read once a
-// step.
+// Fixed-sweep rollouts and steps: WAVES = 2 keeps the kernel within 256
+// registers, so that two waves share a SIMD (the host takes it for models that
+// have them, see waves_per_simd).  Unbounded they take 266 to 286; the values
+// over are per-env ones that are kept in scratch memory (8 to 76 bytes per
+// lane) and read once a step.
 template <int TEAM, int SOLVE, int WAVES>
 __global__ __launch_bounds__(64, WAVES) void k_rollout(DevModel M, TileSet ts, RolloutArgs a) {
   extern __shared__ float lds[];
@@ -261,10 +261,8 @@ __global__ __launch_bounds__(64) void k_rollout_keep(DevModel M, TileSet ts, Rol
   }
 }
 
-// (Fixed sweeps: two waves per SIMD, which costs a step of few envs nothing
-// that is measured: 64 arms 42.2 and 42.3 us.)
-template <int TEAM, int SOLVE>
-__global__ __launch_bounds__(64, SOLVE ? 1 : 2) void k_step(DevModel M, TileSet ts, StepArgs a) {
+template <int TEAM, int SOLVE, int WAVES>
+__global__ __launch_bounds__(64, WAVES) void k_step(DevModel M, TileSet ts, StepArgs a) {
   extern __shared__ float lds[];
   TeamGPU tm = make_team<TEAM>();
   setup_shared(tm, M, lds, ts.env_floats, SOLVE != 0);
@@ -343,8 +341,9 @@ hipError_t TeamLaunch<TEAM>::rollout_keep(const DevModel& M, const TileSet& ts, 
 template <int TEAM>
 hipError_t TeamLaunch<TEAM>::step(const DevModel& M, const TileSet& ts, int grid, size_t lds, const StepArgs& a,
                                   hipStream_t st) {
-  return M.solve_mode ? launch_one(k_step<TEAM, 1>, M, ts, a, grid, lds, st)
-                      : launch_one(k_step<TEAM, 0>, M, ts, a, grid, lds, st);
+  if (M.solve_mode) return launch_one(k_step<TEAM, 1, 1>, M, ts, a, grid, lds, st);
+  return ts.waves > 1 ? launch_one(k_step<TEAM, 0, 2>, M, ts, a, grid, lds, st)
+                      : launch_one(k_step<TEAM, 0, 1>, M, ts, a, grid, lds, st);
 }
 template <int TEAM>
 hipError_t TeamLaunch<TEAM>::grad(const DevModel& M, const TileSet& ts, int grid, size_t lds, const GradArgs& a,
@@ -361,10 +360,10 @@ hipError_t TeamLaunch<TEAM>::recompute(const DevModel& M, const TileSet& ts, int
 template <int TEAM>
 hipError_t TeamLaunch<TEAM>::allow_lds(int bytes) {
   const void* kerns[] = {(const void*)k_rollout<TEAM, 0, 1>,   (const void*)k_rollout<TEAM, 0, 2>,
-                         (const void*)k_rollout<TEAM, 1, 1>,   (const void*)k_step<TEAM, 0>,
-                         (const void*)k_step<TEAM, 1>,         (const void*)k_rollout_grad<TEAM, 0>,
-                         (const void*)k_rollout_grad<TEAM, 1>, (const void*)k_recompute<TEAM>,
-                         (const void*)k_rollout_keep<TEAM>};
+                         (const void*)k_rollout<TEAM, 1, 1>,   (const void*)k_step<TEAM, 0, 1>,
+                         (const void*)k_step<TEAM, 0, 2>,      (const void*)k_step<TEAM, 1, 1>,
+                         (const void*)k_rollout_grad<TEAM, 0>, (const void*)k_rollout_grad<TEAM, 1>,
+                         (const void*)k_recompute<TEAM>,       (const void*)k_rollout_keep<TEAM>};
   for (const void* k : kerns) {
     const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e != hipSuccess) return e;
