@@ -21,7 +21,7 @@ struct HostEnv {
   std::vector<int> topo;   // jpar, jchi, gbody, pcode, colstart, cand
   std::vector<float> cst;
   int team = 1, team_min = 1;
-  int fwd_floats = 0, adj_floats = 0, adj_floats_saved = 0;
+  int fwd_floats = 0, adj_floats = 0, adj_floats_saved = 0, cen_floats = 0;
   int dump_floats = 0;     // one step's saved working set (see drivers.h)
 };
 
@@ -210,10 +210,14 @@ sim_status build_env(const sim_model_desc& d, int e, bool keep_v, HostEnv& H) {
     ma = mlp_adj_floats(d.mlp_sizes[0], d.mlp_sizes[1], d.mlp_sizes[2], d.mlp_sizes[3]);
   }
   const int vs = vsave_floats(keep_v, H.nb);
-  H.fwd_floats = make_lay(H.nb, H.nj, H.G, H.P, H.ncol, H.ncand, H.nj + H.ccap, H.nslot, H.lam, d.n_iters, false, mf, ma, vs).total;
-  H.adj_floats = make_lay(H.nb, H.nj, H.G, H.P, H.ncol, H.ncand, H.nj + H.ccap, H.nslot, H.lam, d.n_iters, true, mf, ma, vs).total;
-  H.adj_floats_saved =
-      make_lay(H.nb, H.nj, H.G, H.P, H.ncol, H.ncand, H.nj + H.ccap, H.nslot, H.lam, d.n_iters, true, mf, ma, vs, true).total;
+  H.cen_floats = centre_floats(H.nb, H.P);
+  auto floats = [&](bool adj, bool ghist) {
+    return make_lay(H.nb, H.nj, H.G, H.P, H.ncol, H.ncand, H.nj + H.ccap, H.nslot, H.lam, d.n_iters, adj, mf, ma, vs,
+                    ghist, H.cen_floats).total;
+  };
+  H.fwd_floats = floats(false, false);
+  H.adj_floats = floats(true, false);
+  H.adj_floats_saved = floats(true, true);
   H.dump_floats = dump_stride_of(H.fwd_floats, d.n_iters, H.nslot, H.nb);
   return SIM_OK;
 }
@@ -255,7 +259,7 @@ sim_status pack_model(const sim_model_desc* d, PackedModel& P, std::string& err)
     hd[H_LAMOFF] = P.lam_off[e]; hd[H_LAMSZ] = H.lam; hd[H_G] = H.G; hd[H_P] = H.P; hd[H_NCOL] = H.ncol;
     hd[H_TOPO] = (int)P.topo.size(); hd[H_CST] = (int)P.cst.size(); hd[H_T] = d->T_env[e];
     hd[H_LB] = d->loss_body[e] - d->env_body_off[e]; hd[H_CCAP] = H.ccap; hd[H_NCAND] = H.ncand;
-    hd[H_ENV] = e; hd[H_NSLOT] = H.nslot;
+    hd[H_ENV] = e; hd[H_NSLOT] = H.nslot; hd[H_CEN] = H.cen_floats;
     sz_replay[e] = (long long)d->ckpt_every * (18 * H.nb + H.lam);
     sz_segment[e] = (long long)d->ckpt_every * H.dump_floats;
     sz_traj[e] = (long long)d->T_env[e] * H.dump_floats + SEG_TAIL;

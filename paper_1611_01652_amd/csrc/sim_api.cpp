@@ -328,6 +328,8 @@ bool make_streams(sim_model* h, int n, int queues) {
     if (!(ok = create(&s))) break;
     const int k = (int)h->streams.size();
     const long long ticks = 10000 + 2500 * k;   // of the 100 MHz clock
+    // (the new stream's first launch, which may set it up, is not part of it)
+    ok = launch_zero(flag, 1, s) == hipSuccess && hipStreamSynchronize(s) == hipSuccess;
     for (int i = 0; ok && i < k; ++i)
       ok = launch_wait_flag(flag, t, seen_dev + i, ticks, h->streams[i]) == hipSuccess;
     ok = ok && launch_set_flag(flag, t, s) == hipSuccess;

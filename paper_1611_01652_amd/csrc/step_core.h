@@ -96,7 +96,7 @@ SHD void kahan_add(float* sum, float* c, float x) {
 // ------------------------------------------------------------------ model in global memory
 // (H_RING is read by nothing here; the host test harness writes it)
 enum { H_B0, H_NB, H_J0, H_NJ, H_LAMOFF, H_LAMSZ, H_G, H_P, H_NCOL, H_TOPO, H_CST, H_T, H_LB, H_CCAP,
-       H_NCAND, H_ENV, H_SEG, H_NSLOT, H_TAPE, H_RING, H_COUNT };
+       H_NCAND, H_ENV, H_SEG, H_NSLOT, H_TAPE, H_RING, H_CEN, H_COUNT };
 // candidate code: kind in the top byte
 enum { K_JOINT = 0, K_GROUND = 1, K_PAIR = 2 };
 SHD int cand_kind(int c) { return c >> 24; }
@@ -198,22 +198,24 @@ enum { JA_DAMP = 0, JA_DAMPC = 1, JA_ANCP = 2, JA_ANCC = 5, JA_ANC_COMP = 6, JA_
 // vs_f: floats of saved predicted velocities (learned warm start, restitution), 0 without
 // ghist: the reverse reads the sweeps' impulse history from the saved working
 // sets in global memory; otherwise (replays) the adjoint layout holds it
-// The row set-up's sphere centres (cen) are kept where the env has at least
-// two candidate pairs per body, each centre then taking part in four tests or
-// more.  With fewer they would save little and could make the layout of a
-// large env exceed the LDS (460 bodies, three of them with a sphere-sphere
-// sphere: 159 KB without, 164 KB with them); a test forms its two centres.
-SHD bool keeps_centres(int nb, int P) { return P >= 2 * nb; }
+// The row set-up's sphere centres (cen) are kept in envs of up to six bodies
+// with a candidate pair, and where there are at least two pairs per body, each
+// centre then taking part in four tests or more.  With fewer they would save
+// little and could make the layout of a large env exceed the LDS (460 bodies,
+// three of them with a sphere-sphere sphere: 159 KB without, 164 KB with them);
+// a test forms its two centres.  (Decided when the model is packed.)
+SHD int centre_floats(int nb, int P) { return P >= 2 * nb || (P > 0 && nb <= 6) ? 4 * nb : 0; }
+// cen_f: floats of the row set-up's sphere centres
 SHD Lay make_lay(int nb, int nj, int G, int P, int ncol, int ncand, int nvis, int nslot, int lam, int n_iters,
                  bool adj,
-                 int mlp_f = 0, int mlp_a = 0, int vs_f = 0, bool ghist = false) {
+                 int mlp_f, int mlp_a, int vs_f, bool ghist, int cen_f) {
   Lay L;
   int o = 0;
   L.jc = o; o += align4(nj * JS);
   L.gs = o; o += align4(G * 4);
   L.topo = o; o += align4(2 * nj + G + P + ncol + 1 + ncand);
   L.misc = o; o += MISC_N;
-  L.cen = o; o += keeps_centres(nb, P) ? 4 * nb : 0;
+  L.cen = o; o += cen_f;
   L.body = o; o += align4((nb + 1) * BS);   // bodies and the world slot (index nb)
   L.ctl = o; o += align4(nj);
   L.ws = o; o += align4(lam);
@@ -273,9 +275,10 @@ struct Env {
   // joint (the same each step), then the placed contacts in canonical order
   SHD i4* plan() const { return (i4*)(L + lay.plan); }
   SHD i4* vis() const { return (i4*)(L + lay.vis); }
-  // (row set-up, with keeps_centres) world centre and radius of each body's
-  // sphere-sphere sphere
+  // (row set-up, where the env keeps centres) world centre and radius of each
+  // body's sphere-sphere sphere
   SHD float* cen(int b) const { return L + lay.cen + 4 * b; }
+  SHD bool keeps_centres() const { return lay.body > lay.cen; }   // (the bodies follow them)
   SHD float* ctl() const { return L + lay.ctl; }   // the step's control of each joint
   SHD float* misc() const { return L + lay.misc; }
   SHD float* jA() const { return L + lay.jA; }
@@ -367,7 +370,7 @@ SHD Env make_env(const DevModel& M, int ie, float* lds, int n_iters, bool adj) {
   E.lay = make_lay(E.nb, E.nj, E.G, E.P, E.ncol, E.ncand, E.nj + E.ccap, E.nslot, E.lam_size, n_iters, adj,
                    mlp_floats_fwd(M),
                    mlp_floats_adj(M), vsave_floats(M.ws_kind || M.has_rest, E.nb),
-                   M.dump != DUMP_REPLAY);
+                   M.dump != DUMP_REPLAY, h[H_CEN]);
   return E;
 }
 
@@ -834,7 +837,7 @@ SHD f4 pair_sphere(const Env& E, int b) {
 // Candidates are tested in canonical order, a lane each and as many at a time
 // as the team has lanes (whatever their colour: a colour of a long chain holds
 // a dozen pairs, few of them near, and a pass per colour spent most of the
-// row set-up on its latency).  Where an env has pairs enough (keeps_centres)
+// row set-up on its latency).  Where an env has pairs enough (centre_floats)
 // the sphere centres are formed once per body, and a pair whose squared distance is clearly out of reach takes no root.  The
 // k-th active candidate takes the k-th row slot; beyond the env's capacity it
 // is dropped, its stored impulse cleared and the env flagged.  (Chains of 2..32
@@ -853,7 +856,7 @@ SHD void f_rows(const Team& tm, const DevModel& M, const Env& E, bool act) {
   // at once, lanes over joints.
   const int nj = act ? E.nj : 0;
   for (int j = tm.tl; j < nj; j += tm.ts) build_joint(M, E, j, E.jr * j);
-  const bool centres = keeps_centres(E.nb, E.P);
+  const bool centres = E.keeps_centres();
   if (centres)
     for (int b = tm.tl; b < (act ? E.nb : 0); b += tm.ts) st4(E.cen(b), pair_sphere(E, b));
   tm.sync();
@@ -876,7 +879,15 @@ SHD void f_rows(const Team& tm, const DevModel& M, const Env& E, bool act) {
       } else {
         f4 ca, cb;
         if (centres) { ca = ld4(E.cen(rb.a)); cb = ld4(E.cen(rb.b)); }
-        else { ca = pair_sphere(E, rb.a); cb = pair_sphere(E, rb.b); }
+        else [[unlikely]] {
+          // (kept short and out of line: in line it slowed the calls of models
+          // that never come here by up to 0.8 %, 256 balls 11.56 -> 11.65 ms)
+#pragma unroll 1
+          for (int side = 0; side < 2; ++side) {
+            ca = cb;
+            cb = pair_sphere(E, side ? rb.b : rb.a);
+          }
+        }
         const f3 d = mk3(cb.x, cb.y, cb.z) - mk3(ca.x, ca.y, ca.z);
         const float reach = (ca.w + cb.w + M.spec) * 1.0001f;
         if (!(reach > 1e-3f) || !(dot(d, d) > reach * reach)) on = len3(d) - ca.w - cb.w < M.spec;

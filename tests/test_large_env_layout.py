@@ -1,11 +1,12 @@
 """The LDS an env needs where few of its bodies have a sphere-sphere sphere.
 
-The row set-up keeps the spheres' world centres in LDS only for envs with two
-candidate pairs per body or more.  The layouts of large envs with few pairs
-must stay within a workgroup's 160 KB (an env that does not fit is refused by
-sim_init): 460 free bodies, three of them with a sphere-sphere sphere, need
-159 KB in every reverse mode, and 164 KB if every body had a centre.  The
-steps and gradients are the oracle's on both sides of the rule."""
+The row set-up keeps the spheres' world centres in LDS for envs with two
+candidate pairs per body or more, and for those of up to six bodies.  The
+layouts of large envs with few pairs must stay within a workgroup's 160 KB (an
+env that does not fit is refused by sim_init): 460 free bodies, three of them
+with a sphere-sphere sphere, need 159 KB in every reverse mode, and 164 KB if
+every body had a centre.  The steps and gradients are the oracle's on both
+sides of the rule."""
 import numpy as np
 import pytest
 
@@ -43,8 +44,8 @@ def test_large_env_with_few_pairs_fits(mode):
     assert 4 * max(_stride(sz["fwd_floats"]), _stride(sz["adj_floats"])) <= LDS_BYTES
 
 
-# pairs per body: 3/8 and 10/6 (centres formed per test), 15/7 (kept)
-@pytest.mark.parametrize("n,n_pair", [(8, 3), (6, 5), (7, 6)])
+# pairs per body: 3/8 and 10/7 (centres formed per test), 15/7 and 10/6 (kept)
+@pytest.mark.parametrize("n,n_pair", [(8, 3), (7, 5), (7, 6), (6, 5)])
 def test_pairs_on_both_sides_of_the_rule_equal_the_oracle(n, n_pair):
     w = _spheres(n, n_pair, T=30, spread=0.12)
     got, o = host_fp64(w), Oracle(w)
