@@ -75,3 +75,29 @@ def test_queued_tolerance_steps_equal_a_small_model_s(n):
     for i, e in enumerate(some):
         assert torch.equal(x[:, 2 * e:2 * e + 2], xb[:, 2 * i:2 * i + 2]), e
     sb.close()
+
+
+def test_recurrent_units_carry_through_the_steps_of_a_graph():
+    print("case step graph, recurrent controller", flush=True)
+    w = W.quadruped(n_envs=24, T_min=4, T_max=4, rec=3,
+                    mlp_w=W.mlp_init(W.rec_sizes(W.MLP_SIZES, 3), zero_output=False, out_scale=0.3))
+    s = Simulator(w)
+    x0, _ = to_dev(w)
+    u = torch.tensor(np.asarray(w.extra["mlp"]["w"], np.float32), device="cuda")
+    xs, le, fe = [x0], torch.zeros(s.info.lam_size, device="cuda"), None
+    for k in range(4):
+        xk, le, fe = s.step(xs[-1], u, le, k)
+        xs.append(xk)
+    buf = torch.zeros((2,) + tuple(x0.shape), device="cuda")
+    lam, flags = torch.zeros_like(le), torch.zeros_like(fe)
+    g = s.step_graph(4, buf, u, lam, flags=flags)
+    for _ in range(3):
+        buf[0].copy_(x0)
+        buf[1].fill_(7.0)
+        lam.zero_()
+        g.launch()
+        torch.cuda.synchronize()
+        assert torch.equal(buf[0], xs[4]) and torch.equal(buf[1], xs[3])
+        assert torch.equal(lam, le) and torch.equal(flags, fe)
+    g.close()
+    s.close()
