@@ -838,11 +838,12 @@ SHD f4 pair_sphere(const Env& E, int b) {
 // as the team has lanes (whatever their colour: a colour of a long chain holds
 // a dozen pairs, few of them near, and a pass per colour spent most of the
 // row set-up on its latency).  Where an env has pairs enough (centre_floats)
-// the sphere centres are formed once per body, and a pair whose squared distance is clearly out of reach takes no root.  The
-// k-th active candidate takes the k-th row slot; beyond the env's capacity it
-// is dropped, its stored impulse cleared and the env flagged.  (Chains of 2..32
-// bodies, forward step: 45 of 103 thousand cycles per wave in a pass per
-// colour; the whole forward-and-reverse call 63.0 -> 58.0 ms.)
+// the sphere centres are formed once per body, and a pair whose squared
+// distance is clearly out of reach takes no root.  The k-th active candidate
+// takes the k-th row slot; beyond the env's capacity it is dropped, its stored
+// impulse cleared and the env flagged.  (Chains of 2..32 bodies, forward step:
+// 45 of 103 thousand cycles per wave in a pass per colour; the whole
+// forward-and-reverse call 63.0 -> 58.0 ms.)
 //
 // The sweep plan lists the step's visits: each joint colour, then the placed
 // contacts split into the longest runs of the canonical order in which no two
