@@ -303,10 +303,17 @@ int hw_queues() {
 // queues, so that two of four buckets run in turn (333 chains by segments:
 // 18.1 instead of 9.2 ms per call).  Which queue a stream has cannot be asked,
 // so it is tried: kernels on the streams chosen so far wait for one on the new
-// stream, for at most 100 us and 25 us for each of them; if some of them does
+// stream, for at most 100 us and 25 us for each of them.  If one of them does
 // not see it, the two share a queue (or the device is busy) and another stream
-// is tried.  After max(8, twice the streams wanted) tries any streams are
-// taken: the waits sum to 1.4 ms at most for four streams, 14 ms for 15.
+// is tried.  If several do not, the device or the host is busy, since the chosen
+// streams have queues of their own, and the try counts as three.  After
+// kMisses misses the rest are taken untried, those that missed first.  So no
+// more than kMisses - 1 streams are made beyond those wanted: where HIP may use
+// many queues each new stream takes one more of them for good, and past what
+// the hardware holds their kernels are swapped in and out (15 streams wanted
+// and 31 made when every try had failed, kernels being traced one at a time:
+// up to 20 times the waves, each bucket's kernel up to 60 % longer).
+constexpr int kMisses = 8;
 bool make_streams(sim_model* h, int n, int queues) {
   auto create = [](hipStream_t* s) { return hipStreamCreateWithFlags(s, hipStreamNonBlocking) == hipSuccess; };
   const int want = std::min(n, queues);
@@ -322,8 +329,7 @@ bool make_streams(sim_model* h, int n, int queues) {
     ok = launch_set_flag(flag, 1, first) == hipSuccess &&
          launch_wait_flag(flag, 1, seen_dev, 0, first) == hipSuccess && hipStreamSynchronize(first) == hipSuccess;
   }
-  const int last = 1 + std::max(8, 2 * want);
-  for (int t = 2; ok && (int)h->streams.size() < want && t <= last; ++t) {
+  for (int t = 2, missed = 0; ok && (int)h->streams.size() < want && missed < kMisses; ++t) {
     hipStream_t s;
     if (!(ok = create(&s))) break;
     const int k = (int)h->streams.size();
@@ -336,14 +342,24 @@ bool make_streams(sim_model* h, int n, int queues) {
     for (int i = 0; i < k; ++i) ok = hipStreamSynchronize(h->streams[i]) == hipSuccess && ok;
     ok = hipStreamSynchronize(s) == hipSuccess && ok;
     ok = ok && hipMemcpy(seen.data(), seen_dev, k * sizeof(int), hipMemcpyDeviceToHost) == hipSuccess;
-    bool alone = ok;
-    for (int i = 0; i < k; ++i) alone = alone && seen[i] == t;
-    (alone ? h->streams : spare).push_back(s);
+    int blind = 0;
+    for (int i = 0; i < k; ++i) blind += seen[i] != t;
+    if (ok && blind == 0) {
+      h->streams.push_back(s);
+    } else {
+      spare.push_back(s);
+      missed += blind > 1 ? 3 : 1;
+    }
   }
-  // (fewer queues found than asked for: any of the streams)
-  while (ok && (int)h->streams.size() < want && !spare.empty()) {
-    h->streams.push_back(spare.back());
-    spare.pop_back();
+  while (ok && (int)h->streams.size() < want) {
+    hipStream_t s;
+    if (!spare.empty()) {
+      s = spare.back();
+      spare.pop_back();
+    } else if (!(ok = create(&s))) {
+      break;
+    }
+    h->streams.push_back(s);
   }
   for (hipStream_t s : spare) (void)hipStreamDestroy(s);
   return ok;
