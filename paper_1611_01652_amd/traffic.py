@@ -128,7 +128,7 @@ def summarize(workload, d, kernel="k_rollout_grad", buckets=None):
         bw = by_bucket(os.path.join(d, f"pmc_{workload}_w"), "WRITE_SIZE", kernel, buckets)
         out["bytes_per_launch_by_bucket"] = [(f / sf + w / sw) * 1024.0 for f, w in zip(bf, bw)]
     # the other kernels of the gradient and the forward, when the run has them
-    for other in ("k_recompute", "k_rollout<", "k_rollout_keep", "k_render("):
+    for other in ("k_recompute", "k_rollout<", "k_rollout_keep", "k_render<"):
         try:
             of, _, _ = per_dispatch(read_counters(os.path.join(d, f"pmc_{workload}_f"), "FETCH_SIZE"),
                                     lambda k: other in k)
