@@ -1821,6 +1821,11 @@ SHD void f_pgs_tol(const Team& tm, const DevModel& M, const Env& E, bool live, i
     else contact_load<true>(cr, E, h.vc.x, h.vc.y, h.vc.z);
   }
   tm.sync();
+  // (the sweeps' loop starts on a 64-byte line: hundreds of turns per step, and
+  // a shift of the code by 16 bytes changed 512 chains' solves by 1 to 2 %)
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile(".p2align 6");
+#endif
   for (;;) {
     const bool run = live && res > M.tol && it < limit;
     if (!tm.any(run)) break;
